@@ -34,12 +34,9 @@ METRIC = "grid-point updates/s & % HBM peak (AT step, adjoint, batched) vs plain
 # WRITE_SIZE x 1.0 (scales from a plain 1 GiB copy); reported only while the
 # kernel source hashes to the value the counters were taken on, and null
 # (bytes_per_launch None) until they have been taken on the current source.
-TRAFFIC = {"sources": ["paper_1911_05769_amd/csrc/at_step1d.hip",
+TRAFFIC = {"sources": ["paper_1911_05769_amd/csrc/at_wave1d.h",
                        "paper_1911_05769_amd/csrc/at_stencil1d.h"],
-           "md5": "1a8eca99f62c6fbc1b646766206a9922", "fuse": 56,
-           # FETCH_SIZE 73249.3 KiB x 2.0 + WRITE_SIZE 132608.0 KiB x 1.0, mean of the 35
-           # 56-step launches of one 2000-step run
-           "bytes_per_launch": 285805158.4}
+           "md5": None, "fuse": 56, "bytes_per_launch": None}
 
 
 def eprint(*a):
@@ -361,7 +358,7 @@ def main():
                    "fuse_steps": main_res["s"], "points_per_thread": main_res["ppt"],
                    "arith": "exact order, no contraction",
                    "kernel": ("k_step1d_plain<4,false,false>" if main_res["s"] == 1
-                              else "k_step1d_aligned<4,false,false,%d>" % main_res["ppt"])},
+                              else "k_wave1d<4,false,false,%d,...>" % main_res["ppt"])},
         "roofline": rl,
         "roofline_other": rl_other,
         "timing": dict(spread(main_res["run_ms"]), clock="HIP events around each 2000-step run"),

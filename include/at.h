@@ -146,9 +146,10 @@ void at_free(at_ctx *ctx);
 at_status at_step(at_ctx *ctx, const double *u_in, double *u_out);
 
 /* Advance nsteps steps from the current level held in u; the result is left
- * in u.  scratch is a second field of the same size.  Steps are fused s at a
- * time (fuse_steps or the autotuned value); results are bit-identical for
- * every s.  A 1D launch of s steps writes to the ring the tile edges of its
+ * in u.  scratch is a second field of the same size.  Steps are fused up to s
+ * at a time (fuse_steps or the autotuned value, as far as the kernel's regions
+ * allow), a run's steps spread evenly over its launches; results are
+ * bit-identical for every s.  A 1D launch of s steps writes to the ring the tile edges of its
  * last L + m - 1 levels (the levels a later step reads; earlier ones stay in
  * the launch's LDS history), or of every level in record mode, where the ring
  * is the adjoint's edge tape.  Record mode also stores a checkpoint of u
@@ -211,12 +212,12 @@ at_status at_set_graph(at_ctx *ctx, int32_t use_graph);
 #define AT_DEBUG_POISON_RING 1
 at_status at_set_debug(at_ctx *ctx, int32_t flags);
 
-/* Choose the launch shape -- 1D: points per thread (the variant, 16, 8 or 4
- * among those dividing the tile width) together with steps per launch s, and
- * the whole-grid variant 4 where the grid fits one workgroup; 3D:
+/* Choose the launch shape -- 1D: points per thread (the variant; 32, 16, 8 or
+ * 4) together with steps per launch s, and the whole-grid variant 4 where the
+ * grid fits one workgroup; 3D:
  * the kernel variant (including the two-step variants) -- nothing that
- * changes results -- by timing `trial_steps` steps from u0 for each
- * candidate; requires n == 0 and leaves the context at n = 0 with the ring
+ * changes results -- by timing about `trial_steps` steps (whole launches) from
+ * u0 for each candidate; requires n == 0 and leaves the context at n = 0 with the ring
  * cleared.  u0 is not modified; t1 and t2 are two scratch fields.
  * Synchronises the stream.  *chosen receives s (1D; nsteps_max for variant
  * 4) or the variant (3D); at_query returns both. */
@@ -237,7 +238,8 @@ at_status at_autotune(at_ctx *ctx, const double *u0, double *t1, double *t2,
  * and at_step use a one-step variant); choosing another sets it to 1, and
  * at_set_fuse(ctx, 2) selects 15 (or 16).  1D contexts: 0 automatic; 1, 2, 3 for 16, 8
  * and 4 points per thread in the fused launches (the tile width must be
- * divisible by it, AT_ERR_ARG otherwise); 4 for the whole periodic grid in
+ * divisible by it, AT_ERR_ARG otherwise; 1 also stands for the 32 points that
+ * at_autotune may choose); 4 for the whole periodic grid in
  * one workgroup of 256 threads (N <= 256 x 16, with N and the tile width
  * multiples of the 4, 8 or 16 points a thread holds, AT_ERR_ARG otherwise):
  * no rim is recomputed, the neighbour exchange wraps around the workgroup,
@@ -333,8 +335,9 @@ at_status at_batch_reset(at_batch *b);
 at_status at_batch_query(const at_batch *b, int64_t *n, int32_t *fuse_steps, int32_t *max_fuse,
                          int32_t *variant);
 
-/* Points per thread of the batched kernel: 0 (default) and 1: 16, 2: 8,
- * 3: 4.  Fewer points per thread make shorter regions (more workgroups, more
+/* Points per thread of the batched kernel: 0 (default) and 1: 16 (or what
+ * at_batch_autotune chose), 2: 8, 3: 4; fewer where a tile would be a single
+ * thread.  Fewer points per thread make shorter regions (more workgroups, more
  * redundant rim work per point).  Steps per launch are lowered to the limit
  * of the new layout if needed.  Every choice gives the same bits. */
 at_status at_batch_set_variant(at_batch *b, int32_t variant);
@@ -342,7 +345,8 @@ at_status at_batch_set_variant(at_batch *b, int32_t variant);
 /* Choose the batch's points per thread and steps per launch by timing (same
  * contract as at_autotune, per batch); *chosen receives the steps per
  * launch, at_batch_query both.  Steps per launch are tried largest first, and
- * a smaller count replaces a larger one only when it is 2% faster. */
+ * a smaller count replaces a larger one only when it is 2% faster; a trial runs
+ * about trial_steps steps, in whole launches. */
 at_status at_batch_autotune(at_batch *b, double *const *u_dev, double *const *t1,
                             double *const *t2, int32_t trial_steps, int32_t *chosen);
 at_status at_batch_set_fuse(at_batch *b, int32_t fuse_steps);

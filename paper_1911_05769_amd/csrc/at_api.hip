@@ -56,26 +56,29 @@ struct Layout {
 struct Derived {
     int dim, order, h, m;
     int L;          // delay bound
-    int fppt = 16;  // 1D: points per thread of the fused (aligned) launches
+    int fppt = 16;  // 1D: points per thread of the regions that limit steps per launch
     int64_t N;      // total points
     int64_t F;      // faces
     int64_t nb;     // tiles / blocks
     int64_t P, W;   // 1D
     double c1[3], c2[3];
+    bool contracted = false;
 };
 
-// Region of one workgroup: RL points left of the owned chunk, CH owned, s*h
-// right.  Aligned form (tile width a multiple of the points per thread): RL
-// and CH are multiples of PPT so every thread's points lie in one tile.
+// Region of a workgroup of 256 threads: RL points left of the owned chunk, CH
+// owned, s*h right; where the tile width is a multiple of the points per
+// thread, RL and CH are multiples of it too.  The one-step and the general
+// kernel run these, and max_fuse_1d measures with them what at_set_fuse
+// accepts (a launch of the fused kernels takes as many of those steps as its
+// own region allows, launch_steps).
 struct Region1D {
-    bool aligned;
-    int ppt;        // points per thread of the kernel that runs it
+    int ppt;        // points per thread
     int64_t RL, CH;
 };
 
-// Points per thread of the fused 1D launches: the most (16, 8, 4) that still
-// give every SIMD four waves of the grid and divide the tile width; 16 (the
-// unaligned kernel) when none divides it.
+// Points per thread that max_fuse_1d's regions are measured at: the most (16,
+// 8, 4) that still give every SIMD four waves of the grid and divide the tile
+// width; 16 when none divides it
 int fused_ppt(const Derived &d)
 {
     const int opts[3] = {16, 8, 4};
@@ -162,6 +165,7 @@ at_status derive(const at_config *c, Derived &d)
         at_status st = at3_check(c);
         if (st != AT_OK) return st;
     }
+    d.contracted = c->arith == 1;
     if (d.dim == 1) d.fppt = fused_ppt(d);
     return AT_OK;
 }
@@ -196,6 +200,7 @@ struct at_ctx {
     int64_t n;
     int fuse;
     int variant;     // 3D kernel variant (tile rows, prefetch depth, register budget)
+    int kind = 0;    // 1D: region kind of the fused launches (fused_shape), 0 automatic
     int adj_fuse = 0;   // reverse steps per adjoint launch: 0 automatic, 1 one-step kernel
     int debug = 0;      // AT_DEBUG_* flags (at_set_debug)
     // graph replay of at_run (at_set_graph): the launch sequence of one call,
@@ -257,7 +262,7 @@ at_status make_layout(const at_config *c, const Derived &d, Layout &L)
     return AT_OK;
 }
 
-Region1D region_1d(const Derived &d, int s, bool allow_plain = true);
+Region1D region_1d(const Derived &d, int s);
 
 // Largest steps-per-launch usable for this 1D configuration: the owned chunk
 // stays at least half the region (or the whole grid) and the LDS edge
@@ -270,24 +275,22 @@ int max_fuse_1d(const Derived &d)
         const int reg = kThreads * rg.ppt;
         if (rg.CH < std::min<int64_t>(reg / 2, d.N)) break;
         const int NT = (int)((reg - 1) / d.W + 2);
-        if (step1d_lds_bytes(d.order, s, NT, d.L + d.m - 1, rg.ppt, false) > 64 * 1024) break;
+        if (step1d_lds_bytes(d.order, s, NT, d.L + d.m - 1, rg.ppt) > 64 * 1024) break;
         best = s;
     }
     return best;
 }
 
-Region1D region_1d(const Derived &d, int s, bool allow_plain)
+Region1D region_1d(const Derived &d, int s)
 {
     // single steps use the 8-point-per-thread kernel when the tiles allow it
-    // (not in the batched form, whose kernel keeps 16 points per thread)
     const int pplain = step1d_plain_points_per_thread();
-    const bool plain = allow_plain && s == 1 && d.W % pplain == 0;
+    const bool plain = s == 1 && d.W % pplain == 0;
     const int ppt = plain ? pplain : (d.W % d.fppt == 0 ? d.fppt : step1d_points_per_thread());
     const int64_t reg = (int64_t)kThreads * ppt;
     Region1D r;
     r.ppt = ppt;
-    r.aligned = d.W % ppt == 0;
-    if (r.aligned) {
+    if (d.W % ppt == 0) {
         r.RL = ((int64_t)s * d.h + ppt - 1) / ppt * ppt;
         r.CH = (reg - r.RL - (int64_t)s * d.h) / ppt * ppt;
     } else {
@@ -298,6 +301,83 @@ Region1D region_1d(const Derived &d, int s, bool allow_plain)
     return r;
 }
 
+// A region of the fused kernels (at_wave1d.h) for s steps.  kind: 32, 16, 8, 4
+// are the points per thread of a one-wave region, kWide the four-wave region
+// at 16.  ok is false when the tile width is not a sum of threads of ppt and
+// ppt - 1 points (a few widths below ppt * (ppt - 2)), when one thread is a
+// whole tile, when s is more than the rims allow, or when the LDS tables of
+// very narrow tiles exceed 64 KiB.
+constexpr int kWide = -16;
+
+struct FusedShape {
+    bool ok = false;
+    int ppt = 0, nw = 0, tpt = 0, nf = 0, RT = 0, CT = 0, NT = 0;
+    int64_t nblocks = 0;
+    size_t lds = 0;
+};
+
+FusedShape fused_shape(const Derived &d, int s, int kind)
+{
+    FusedShape w;
+    if (kind == 0 || d.W > ((int64_t)1 << 30)) return w;
+    const int ppt = std::abs(kind), nw = kind < 0 ? 4 : 1, threads = 64 * nw;
+    const int64_t tpt = (d.W + ppt - 1) / ppt, nf = d.W - tpt * (ppt - 1);
+    const int64_t nth = d.P * tpt;
+    if (nf < 1 || nth >= ((int64_t)1 << 31) - 256) return w;
+    if (kind < 0 && nf != tpt) return w;              // (built for whole threads only)
+    if (tpt == 1 && d.W != 4) return w;               // a lane has one face (two at 4 points only)
+    const int least = nf == tpt ? ppt : ppt - 1;      // points of the shortest thread
+    const int RT = (s * d.h + least - 1) / least;
+    if (least < d.h || RT > threads / 4) return w;    // at least half of the threads own points
+    w.ppt = ppt;
+    w.nw = nw;
+    w.tpt = (int)tpt;
+    w.nf = (int)nf;
+    w.RT = RT;
+    w.CT = (int)std::min<int64_t>(threads - 2 * RT, nth);
+    w.NT = (int)((threads - 2) / tpt + 2);
+    w.nblocks = (nth + w.CT - 1) / w.CT;
+    w.lds = wave1d_lds_bytes(d.order, s, w.NT, d.L + d.m - 1, ppt, nw);
+    w.ok = w.lds <= 64 * 1024;
+    return w;
+}
+
+// The kind of region of a fused launch of s steps: the one asked for where the
+// tiles take it, else (0) by size.  In the exact order the largest grids run
+// four-wave regions (us per step with 2^24 points: 9.1, one wave: 9.8; with
+// 2^22 points one wave: 3.06).  Otherwise the most points per thread that still
+// give enough waves: at 32 points eight per SIMD (contracted, 4th order, at 32
+// and 16 points: 6.96 and 7.26 us with 2^24 grid points, 2.37 and 2.30 with
+// 2^22), below that two per SIMD (order 2 at 16, 8 and 4 points: 0.87, 0.70
+// and 1.02 us with 2^20, 0.57, 0.35 and 0.38 with 2^18).  0 when no region
+// fits this tile width.
+int fused_kind(const Derived &d, int want, int s)
+{
+    if (want != 0 && fused_shape(d, 1, want).ok) return want;
+    if (!d.contracted && d.N >= ((int64_t)1 << 23) && s >= 32 && fused_shape(d, s, kWide).ok)
+        return kWide;
+    int pick = 0;
+    for (int p : {32, 16, 8, 4}) {
+        const FusedShape w = fused_shape(d, 8, p);
+        if (!w.ok) continue;
+        pick = p;
+        if (w.nblocks >= (p == 32 ? 8 : 2) * 1024) break;
+    }
+    return pick;
+}
+
+// Steps the next launch advances when `left` remain and f are wanted per
+// launch: as few launches as f and the region allow (a region keeps at least
+// half of its threads owned), of even length
+int launch_steps(const Derived &d, int want, int f, int64_t left)
+{
+    f = (int)std::min<int64_t>(f, left);
+    const int kind = f > 1 ? fused_kind(d, want, f) : 0;
+    while (kind && f > 1 && !fused_shape(d, f, kind).ok) --f;
+    const int64_t n = (left + f - 1) / f;
+    return (int)((left + n - 1) / n);
+}
+
 // Points per thread of the whole-grid single-workgroup kernel (1D variant 4)
 // for this context, 0 when the grid does not fit one workgroup
 int whole_ppt(const at_ctx *c)
@@ -306,6 +386,11 @@ int whole_ppt(const at_ctx *c)
     if (d.dim != 1) return 0;
     return step1d_whole_ppt(d.N, d.W, d.P, d.order, c->cfg.L + d.m - 1);
 }
+
+// Points per thread of the launches that rebuild a checkpoint segment for the
+// adjoint: they write every level straight from registers, coalesced only for
+// few points per thread
+constexpr int kRebuildKind = 4;
 
 at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int s, int publish,
                     double *levels = nullptr)
@@ -343,9 +428,14 @@ at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int 
                                    whole_ppt(c), c->st));
         return AT_OK;
     }
+    // the fused kernels' regions, except for single steps of widths that the
+    // one-step kernel takes and for the few widths the regions do not fit
+    const bool plain = s == 1 && !levels && d.W % step1d_plain_points_per_thread() == 0;
+    const int want = levels ? kRebuildKind : c->kind;
+    const FusedShape ws = plain ? FusedShape() : fused_shape(d, s, fused_kind(d, want, s));
     const Region1D rg = region_1d(d, s);
     const int reg = kThreads * rg.ppt;
-    Step1D a;
+    Step1D a{};
     a.uin = uin;
     a.uout = uout;
     a.ring = c->ring;
@@ -365,7 +455,7 @@ at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int 
     a.slot0 = (int32_t)(n0 % a.R);
     a.D = c->cfg.L + d.m - 1;
     a.levels = levels;
-    if (levels && !rg.aligned) return fail(AT_ERR_STATE, "level store needs the aligned layout");
+    if (levels && !ws.ok) return fail(AT_ERR_STATE, "level store needs the fused kernels");
     a.nu = c->cfg.nu;
     a.dt = c->cfg.dt;
     a.c1 = d.c1[0];
@@ -373,9 +463,19 @@ at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int 
     a.cadv = c->cfg.adv_speed;
     a.A1 = a.dt * a.c1;
     a.A2 = a.dt * (a.nu * a.c2);
+    if (ws.ok) {
+        a.tpt = ws.tpt;
+        a.nf = ws.nf;
+        a.CT = ws.CT;
+        a.RT = ws.RT;
+        a.NT = ws.NT;
+        AT_HIP(launch_wave1d(a, d.order, c->cfg.adv_mode == 1, c->cfg.arith == 1, ws.ppt,
+                             ws.nw, ws.nblocks, c->st));
+        return AT_OK;
+    }
     const int64_t nblocks = (d.N + a.CH - 1) / a.CH;
-    AT_HIP(launch_step1d(a, d.order, c->cfg.adv_mode == 1, rg.aligned, c->cfg.arith == 1, rg.ppt,
-                         nblocks, c->st));
+    AT_HIP(launch_step1d(a, d.order, c->cfg.adv_mode == 1, plain, c->cfg.arith == 1, nblocks,
+                         c->st));
     return AT_OK;
 }
 
@@ -473,6 +573,15 @@ void drop_graph(at_ctx *c)
     if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
     c->gexec = nullptr;
     c->g_n0 = c->g_nsteps = -1;
+}
+
+// Steps of a tuning trial: whole launches of the candidate's s steps, compared
+// per step (a run splits its steps evenly over its launches, so a trial of the
+// same length for all would make candidates alike)
+int trial_length(int trial, int s, int64_t most)
+{
+    const int64_t up = ((int64_t)trial + s - 1) / s * s;
+    return (int)(up <= most ? up : (trial >= s ? trial / s * s : trial));
 }
 
 // Region of a fused reverse launch of s steps (8 points per thread, aligned)
@@ -694,6 +803,7 @@ at_status at_set_variant(at_ctx *c, int32_t v)
         if (p && c->d.W % p != 0)
             return fail(AT_ERR_ARG, "variant %d needs a tile width divisible by %d", v, p);
         c->d.fppt = p ? p : fused_ppt(c->d);
+        c->kind = p == 16 && fused_kind(c->d, 0, 32) == kWide ? kWide : p;
         c->fuse = std::min(c->fuse, max_fuse(c));
     } else {
         c->fuse = at3_is_fused(v) ? 2 : 1;   // 3D: two-step variants advance two steps per launch
@@ -745,12 +855,15 @@ at_status run_launches(at_ctx *c, double *u, double *scratch, int64_t nsteps)
         if (sp) return sp;
     }
     while (left > 0) {
-        int64_t s = std::min<int64_t>(c->fuse, left);
+        int64_t todo = left;                  // steps up to the next checkpoint or the end
         if (c->cfg.record) {
             if (c->n % C == 0)
                 AT_HIP(launch_copy(c->ckpt + (c->n / C) * c->d.N, cur, c->d.N, c->st));
-            s = std::min<int64_t>(s, C - c->n % C);
+            todo = std::min<int64_t>(todo, C - c->n % C);
         }
+        int64_t s = std::min<int64_t>(c->fuse, todo);
+        if (c->d.dim == 1 && c->variant != kWholeVariant)
+            s = launch_steps(c->d, c->kind, c->fuse, todo);
         // 1D without the edge tape: only the last L + m - 1 levels of a launch
         // reach the ring (the next launch reads no older level)
         at_status st = launch_any(c, cur, oth, c->n, (int)s,
@@ -925,23 +1038,22 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
     if (c->cfg.record) return fail(AT_ERR_STATE, "autotune is not available in record mode");
     if (trial_steps < 1 || trial_steps > c->cfg.nsteps_max)
         return fail(AT_ERR_ARG, "trial_steps must be in 1..nsteps_max");
-    // 1D: (points per thread, steps per launch) pairs, the points per thread
-    // as the variant (1, 2, 3: 16, 8, 4; those dividing the tile width);
-    // 3D: the kernel variant (one or two steps per launch)
-    std::vector<std::pair<int, int>> cands;       // (variant, steps per launch)
+    // 1D: (points per thread, steps per launch) pairs; 3D: the kernel variant
+    // (one or two steps per launch)
+    std::vector<std::pair<int, int>> cands;       // (points per thread or variant, steps)
     if (c->d.dim == 1) {
-        const Derived keep = c->d;
-        for (int v = 1; v <= 3; ++v) {
-            const int p = v == 1 ? 16 : (v == 2 ? 8 : 4);
-            if (c->d.W % p != 0) continue;
-            c->d.fppt = p;
-            const int mf = max_fuse(c);
-            for (int s : {1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 56, 64})
-                if (s <= mf && (s > 1 || v == 1)) cands.push_back({v, s});   // one step: one kernel
-        }
-        c->d = keep;
-        if (whole_ppt(c) != 0) cands.push_back({kWholeVariant, 0});   // one launch per run
-        if (cands.empty()) cands.push_back({c->variant, 1});
+        const int mf = max_fuse(c);
+        for (int p : {kWide, 32, 16, 8, 4})
+            for (int s : {64, 56, 48, 40, 32, 24, 20, 16, 12, 8, 4}) {
+                if (s > mf || !fused_shape(c->d, s, p).ok) continue;
+                if (p == kWide && (s < 32 || c->d.N < ((int64_t)1 << 22))) continue;
+                cands.push_back({p, s});
+            }
+        if (cands.empty())                                    // widths without such regions
+            for (int s : {64, 32, 16, 8, 4})
+                if (s <= mf) cands.push_back({0, s});
+        cands.push_back({0, 1});
+        if (whole_ppt(c) != 0) cands.push_back({-kWholeVariant, 0});   // one launch per run
     } else {
         for (int v = 0; v < at3_variants(); ++v)
             if (at3_variant_ok(&c->cfg, v)) cands.push_back({v, at3_is_fused(v) ? 2 : 1});
@@ -959,37 +1071,42 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
     at_status st = AT_OK;
     // select a candidate: the variant (1D: points per thread) and steps per launch
     auto choose = [&](std::pair<int, int> vs) {
-        if (c->d.dim == 1 && vs.first == kWholeVariant) {
-            c->d.fppt = fused_ppt(c->d);          // the regular layout, for the adjoint's rebuild
+        if (c->d.dim == 1 && vs.first == -kWholeVariant) {
             c->variant = kWholeVariant;
             c->fuse = (int)std::min<int64_t>(c->cfg.nsteps_max, INT32_MAX);
             return;
         }
-        if (c->d.dim == 1) {
-            const int p = vs.first == 1 ? 16 : (vs.first == 2 ? 8 : 4);
-            c->d.fppt = p;
-        }
         c->variant = vs.first;
         c->fuse = vs.second;
+        if (c->d.dim == 1) {
+            // the variant at_set_variant would take for this many points per
+            // thread (32 is variant 1 too), 0 where it takes none
+            const int p = std::abs(vs.first), v = p >= 16 ? 1 : (p == 8 ? 2 : (p == 4 ? 3 : 0));
+            c->kind = vs.first;
+            c->variant = v && c->d.W % std::min(p, 16) == 0 ? v : 0;
+        }
     };
     for (size_t i = 0; i < cands.size() && st == AT_OK; ++i) {
         float ms_best = 1e30f;
+        choose(cands[i]);
+        const int steps = trial_length(trial_steps, c->fuse, c->cfg.nsteps_max);
         for (int rep = 0; rep < 2 && st == AT_OK; ++rep) {
             hipError_t e = clear_ring(c);
             if (e == hipSuccess) e = launch_copy(t1, u0, field_doubles(c), c->st);
             c->n = 0;
             choose(cands[i]);
             if (e == hipSuccess) e = hipEventRecord(e0, c->st);
-            if (e == hipSuccess) st = at_run(c, t1, t2, trial_steps);
+            if (e == hipSuccess) st = at_run(c, t1, t2, steps);
             if (e == hipSuccess && st == AT_OK) e = hipEventRecord(e1, c->st);
             if (e == hipSuccess && st == AT_OK) e = hipEventSynchronize(e1);
             float ms = 0.f;
             if (e == hipSuccess && st == AT_OK) e = hipEventElapsedTime(&ms, e0, e1);
             if (e != hipSuccess && st == AT_OK)
                 st = fail(AT_ERR_HIP, "at_autotune: %s", hipGetErrorString(e));
-            ms_best = std::min(ms_best, ms);
+            ms_best = std::min(ms_best, ms / (float)steps);
         }
-        if (st == AT_OK && ms_best < best_ms * 0.98f) { best_ms = ms_best; best = cands[i]; }
+        // the larger counts come first: a smaller one has to be 1% faster
+        if (st == AT_OK && ms_best < best_ms * 0.99f) { best_ms = ms_best; best = cands[i]; }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
@@ -1093,11 +1210,11 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
             const int64_t a1 = std::min(a0 + C, nend);
             AT_HIP(launch_copy(c->seg, c->ckpt + (a0 / C) * N, N, c->st));
             // rebuild levels a0+1 .. a1-1: fused launches that also store every
-            // intermediate level (aligned layout), else one launch per step
-            const bool fused = region_1d(d, 2).aligned;
-            const int sr = fused ? max_fuse(c) : 1;
+            // intermediate level, or one launch per step for the tile widths the
+            // fused kernels do not take
+            const int sr = fused_kind(d, kRebuildKind, 2) ? kMaxFuse : 1;
             for (int64_t n = a0; n + 1 < a1;) {
-                const int s = (int)std::min<int64_t>(sr, a1 - 1 - n);
+                const int s = launch_steps(d, kRebuildKind, sr, a1 - 1 - n);
                 at_status st = launch_1d(c, c->seg + (n - a0) * N, c->seg + (n + s - a0) * N, n, s,
                                          0, s > 1 ? c->seg + (n - a0) * N : nullptr);
                 if (st) return st;
@@ -1191,10 +1308,11 @@ struct at_batch {
     std::vector<int> R;
     std::vector<int8_t *> delays;
     std::vector<double *> ring;
-    std::vector<int64_t> ring_doubles;
+    double *ring_all = nullptr;      // the rings are one stretch of the workspace
+    int64_t ring_all_doubles = 0;
     int64_t nsteps_max = 0;   // smallest over the instances
     int max_fuse = 1, fuse = 1;
-    int ppt = 16;             // points per thread of the batched kernel (16, 8 or 4)
+    int kind = 16;            // region kind asked for (fused_shape)
     int variant = 0;          // 0 automatic (16), 1, 2, 3: 16, 8, 4 points per thread
     int mf_ppt[3] = {1, 1, 1};   // steps-per-launch limit for 16, 8, 4 points per thread
     int64_t n = 0;
@@ -1214,7 +1332,7 @@ struct at_batch {
     bool has_graph = false;
     hipGraphExec_t gexec = nullptr;
     int64_t g_n0 = -1, g_nsteps = -1;
-    int g_fuse = 0, g_ppt = 0;
+    int g_fuse = 0, g_kind = 0;
     uint64_t g_key = 0;
 };
 
@@ -1237,23 +1355,46 @@ void drop_graph(at_batch *b)
     b->gexec = nullptr;
 }
 
+// The region kind every instance's tiles take: the one asked for, or fewer
+// points per thread (4 always fits: the tile widths are multiples of 16)
+int batch_kind(const at_batch *b)
+{
+    if (b->kind < 0) return b->kind;                  // the tuner's, which fits
+    for (int p = b->kind; p > 4; p /= 2) {
+        bool ok = true;
+        for (const Derived &d : b->d) ok = ok && d.W % p == 0 && fused_shape(d, 1, p).ok;
+        if (ok) return p;
+    }
+    return 4;
+}
+
+// Steps per launch: the number set, as far as every instance's regions allow
+int batch_fuse(const at_batch *b)
+{
+    const int kind = batch_kind(b);
+    int s = b->fuse;
+    for (const Derived &d : b->d)
+        while (s > 1 && !fused_shape(d, s, kind).ok) --s;
+    return s;
+}
+
 at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *const *scr,
                        uint64_t key)
 {
     const uint64_t k2 = key ^ ((uint64_t)s * 0x9E3779B97F4A7C15ULL) ^
-                        ((uint64_t)b->ppt * 0xD1B54A32D192ED03ULL);
+                        ((uint64_t)b->kind * 0xD1B54A32D192ED03ULL);
     if (b->slot_s[slot] == s && b->slot_key[slot] == k2) return AT_OK;
     drop_graph(b);    // a cached graph reads these tables
-    const int reg = kThreads * b->ppt;
+    const int kind = batch_kind(b);
     std::vector<Step1D> &D = b->hdesc[slot];
     std::vector<int2> &T = b->htbl[slot];
     D.resize(b->count);
     T.clear();
     size_t lds = 0;
     for (int j = 0; j < b->count; ++j) {
-        Derived d = b->d[j];
-        d.fppt = b->ppt;
-        const Region1D rg = region_1d(d, s, false);
+        const Derived &d = b->d[j];
+        const FusedShape ws = fused_shape(d, s, kind);
+        if (!ws.ok) return fail(AT_ERR_STATE, "batch: no region for %d steps per launch", s);
         Step1D &a = D[j];
         a.uin = u[j];
         a.uout = scr[j];
@@ -1263,13 +1404,17 @@ at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *c
         a.P = d.P;
         a.W = d.W;
         a.n0 = 0;
-        a.CH = rg.CH;
+        a.CH = 0;
         a.s = s;
         a.R = b->R[j];
-        a.NT = (int)((reg - 1) / d.W + 2);
+        a.NT = ws.NT;
+        a.tpt = ws.tpt;
+        a.nf = ws.nf;
+        a.CT = ws.CT;
+        a.RT = ws.RT;
         a.stale = b->cfg[j].halo_mode;
         a.publish = 2;        // no edge tape: the last D levels of a launch
-        a.RL = (int32_t)rg.RL;
+        a.RL = 0;
         a.slot0 = 0;          // set per launch by the batched kernel
         a.D = b->cfg[j].L + d.m - 1;
         a.levels = nullptr;
@@ -1280,9 +1425,8 @@ at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *c
         a.cadv = b->cfg[j].adv_speed;
         a.A1 = a.dt * a.c1;
         a.A2 = a.dt * (a.nu * a.c2);
-        const int64_t nch = (d.N + rg.CH - 1) / rg.CH;
-        for (int64_t c = 0; c < nch; ++c) T.push_back(make_int2(j, (int)c));
-        lds = std::max(lds, step1d_lds_bytes(b->order, s, a.NT, a.D, b->ppt, true));
+        for (int64_t c = 0; c < ws.nblocks; ++c) T.push_back(make_int2(j, (int)c));
+        lds = std::max(lds, ws.lds);
     }
     if ((int64_t)T.size() > b->tbl_cap) return fail(AT_ERR_STATE, "batch block table overflow");
     AT_HIP(hipStreamSynchronize(b->st));
@@ -1304,11 +1448,14 @@ at_status batch_launches(at_batch *b, int64_t n0, int64_t nsteps, double *const 
 {
     int flip = 0;
     int64_t done = 0;
-    while (done < nsteps) {
-        const int s = (int)std::min<int64_t>(b->fuse, nsteps - done);
+    const int f = batch_fuse(b), kind = batch_kind(b);
+    while (done < nsteps) {                // launches of even length: two lengths at most
+        const int64_t left = nsteps - done, n = (left + f - 1) / f;
+        const int s = (int)((left + n - 1) / n);
         const int slot = s == b->slot_s[0] ? 0 : 1;
-        AT_HIP(launch_step1d_batch(b->desc_dev[slot], b->tbl_dev[slot], b->slot_blocks[slot],
-                                   b->order, b->linear, b->fma, b->ppt, n0 + done, flip,
+        AT_HIP(launch_wave1d_batch(b->desc_dev[slot], b->tbl_dev[slot], b->slot_blocks[slot],
+                                   b->order, b->linear, b->fma, std::abs(kind), kind < 0 ? 4 : 1,
+                                   n0 + done, flip,
                                    b->slot_lds[slot], stream));
         flip ^= 1;
         done += s;
@@ -1337,7 +1484,7 @@ static at_status batch_layout(const at_config *cfgs, int32_t count, std::vector<
     for (int j = 0; j < count; ++j) {
         at_status st = derive(&cfgs[j], ds[j]);
         if (st) return fail(st, "instance %d: %s", j, g_err.c_str());
-        ds[j].fppt = step1d_points_per_thread();        // the batched kernel's layout
+        ds[j].fppt = step1d_points_per_thread();
         if (cfgs[j].dim != 1) return fail(AT_ERR_ARG, "instance %d: batched form is 1D", j);
         if (cfgs[j].record) return fail(AT_ERR_ARG, "instance %d: record mode not batched", j);
         if (cfgs[j].order != cfgs[0].order || cfgs[j].adv_mode != cfgs[0].adv_mode ||
@@ -1366,16 +1513,14 @@ static at_status batch_layout(const at_config *cfgs, int32_t count, std::vector<
         Rs[j] = cfgs[j].L + ds[j].m - 1 + smax;
         off_delays[j] = off;
         off = align_up(off + (uint64_t)cfgs[j].nsteps_max * (uint64_t)ds[j].F);
+        int64_t most = 0;
+        for (int p : {kWide, 32, 16, 8, 4})
+            for (int s = 1; s <= smax; ++s) most = std::max(most, fused_shape(ds[j], s, p).nblocks);
+        tbl_cap += most;
+    }
+    for (int j = 0; j < count; ++j) {      // the rings together, cleared by one launch
         off_ring[j] = off;
         off = align_up(off + 8ull * (uint64_t)Rs[j] * (uint64_t)ds[j].P * 2 * ds[j].h);
-        int64_t chmin = ds[j].N;
-        for (int i = 0; i < 3; ++i) {
-            Derived d = ds[j];
-            d.fppt = ppts[i];
-            for (int s = 1; s <= mf_ppt[i]; ++s)
-                chmin = std::min<int64_t>(chmin, region_1d(d, s, false).CH);
-        }
-        tbl_cap += (ds[j].N + chmin - 1) / chmin;
     }
     off_desc = off;
     off = align_up(off + 2ull * count * sizeof(Step1D));
@@ -1443,7 +1588,7 @@ at_status at_batch_init(const at_config *cfgs, int32_t count, void *workspace,
     b->d = ds;
     b->R = Rs;
     for (int i = 0; i < 3; ++i) b->mf_ppt[i] = mfp[i];
-    b->ppt = 16;
+    b->kind = 16;
     b->max_fuse = mfp[0];
     b->fuse = cfgs[0].fuse_steps > 0 ? std::min<int>(cfgs[0].fuse_steps, b->max_fuse) : 1;
     b->nsteps_max = cfgs[0].nsteps_max;
@@ -1459,15 +1604,17 @@ at_status at_batch_init(const at_config *cfgs, int32_t count, void *workspace,
         b->nsteps_max = std::min<int64_t>(b->nsteps_max, c->nsteps_max);
         b->delays.push_back((int8_t *)(base + od[j]));
         b->ring.push_back((double *)(base + orr[j]));
-        b->ring_doubles.push_back((int64_t)Rs[j] * ds[j].P * 2 * ds[j].h);
         if (c->delay_mode == AT_DELAY_GENERATE)
             e = launch_delays(b->delays[j], c->nsteps_max, ds[j].F, c->L, ds[j].m, c->delay_dist,
                               c->delay_seed, b->st);
         else if (c->nsteps_max > 0)
             e = hipMemcpyAsync(b->delays[j], c->delays_host, (size_t)(c->nsteps_max * ds[j].F),
                                hipMemcpyHostToDevice, b->st);
-        if (e == hipSuccess) e = launch_fill(b->ring[j], b->ring_doubles[j], 0.0, b->st);
     }
+    // the rings follow each other (batch_layout), so one pass clears them all
+    b->ring_all = (double *)(base + orr[0]);
+    b->ring_all_doubles = (int64_t)((odesc - orr[0]) / 8);
+    if (e == hipSuccess) e = launch_fill(b->ring_all, b->ring_all_doubles, 0.0, b->st);
     if (e == hipSuccess) e = hipStreamSynchronize(b->st);
     if (e != hipSuccess) {
         delete b;
@@ -1500,7 +1647,7 @@ at_status at_batch_set_variant(at_batch *b, int32_t v)
     if (v < 0 || v > 3) return fail(AT_ERR_ARG, "batch variant must be in 0..3");
     const int idx = v <= 1 ? 0 : v - 1;               // 16, 8, 4 points per thread
     b->variant = v;
-    b->ppt = idx == 0 ? 16 : (idx == 1 ? 8 : 4);
+    b->kind = idx == 0 ? 16 : (idx == 1 ? 8 : 4);
     b->max_fuse = b->mf_ppt[idx];
     b->fuse = std::min(b->fuse, b->max_fuse);
     b->slot_s[0] = b->slot_s[1] = 0;                  // tables are rebuilt for the new layout
@@ -1511,8 +1658,7 @@ at_status at_batch_set_variant(at_batch *b, int32_t v)
 at_status at_batch_reset(at_batch *b)
 {
     if (!b) return fail(AT_ERR_ARG, "null batch");
-    for (int j = 0; j < b->count; ++j)
-        AT_HIP(launch_fill(b->ring[j], b->ring_doubles[j], 0.0, b->st));
+    AT_HIP(launch_fill(b->ring_all, b->ring_all_doubles, 0.0, b->st));
     b->n = 0;
     return AT_OK;
 }
@@ -1530,19 +1676,18 @@ at_status at_batch_run(at_batch *b, double *const *u, double *const *scr, int64_
     if (nsteps == 0) return AT_OK;
     const uint64_t key = ptr_key(u, scr, b->count);
     if (use_graph && b->has_graph && b->g_n0 == b->n && b->g_nsteps == nsteps &&
-        b->g_fuse == b->fuse && b->g_ppt == b->ppt && b->g_key == key) {
+        b->g_fuse == b->fuse && b->g_kind == b->kind && b->g_key == key) {
         AT_HIP(hipGraphLaunch(b->gexec, b->st));
         b->n += nsteps;
         return AT_OK;
     }
-    at_status st = batch_tables(b, 0, b->fuse, u, scr, key);
+    // the run's launches are s or s - 1 steps long (batch_launches)
+    const int64_t nl = (nsteps + batch_fuse(b) - 1) / batch_fuse(b);
+    const int s_long = (int)((nsteps + nl - 1) / nl);
+    at_status st = batch_tables(b, 0, s_long, u, scr, key);
     if (st) return st;
-    const int tail = (int)(nsteps % b->fuse);
-    if (tail && nsteps > b->fuse) {
-        st = batch_tables(b, 1, tail, u, scr, key);
-        if (st) return st;
-    } else if (tail) {
-        st = batch_tables(b, 0, tail, u, scr, key);    // a single short launch
+    if (nsteps % nl != 0) {
+        st = batch_tables(b, 1, s_long - 1, u, scr, key);
         if (st) return st;
     }
     if (!use_graph) {
@@ -1566,7 +1711,7 @@ at_status at_batch_run(at_batch *b, double *const *u, double *const *scr, int64_
     b->g_n0 = b->n;
     b->g_nsteps = nsteps;
     b->g_fuse = b->fuse;
-    b->g_ppt = b->ppt;
+    b->g_kind = b->kind;
     b->g_key = key;
     AT_HIP(hipGraphLaunch(b->gexec, b->st));
     b->n += nsteps;
@@ -1580,26 +1725,35 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
     if (b->n != 0) return fail(AT_ERR_STATE, "autotune needs a batch at step 0");
     if (trial_steps < 1 || trial_steps > b->nsteps_max)
         return fail(AT_ERR_ARG, "trial_steps must be in 1..nsteps_max");
-    static const int cands[] = {1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32, 40, 48, 56, 64};
+    static const int cands[] = {1, 4, 8, 12, 16, 20, 24, 28, 32, 40, 48, 56, 64};
     hipEvent_t e0, e1;
     AT_HIP(hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) {
         (void)hipEventDestroy(e0);
         return fail(AT_ERR_HIP, "at_batch_autotune: hipEventCreate failed");
     }
-    // points per thread (variants 1, 2, 3: 16, 8, 4) and steps per launch
+    // points per thread (32 and 16: variant 1; 8: 2; 4: 3) and steps per launch
     float best_ms = 1e30f;
     int best_s = 1, best_v = 1;
     at_status st = AT_OK;
-    for (int v = 1; v <= 3 && st == AT_OK; ++v) {
+    int best_k = 16;
+    for (int k : {kWide, 32, 16, 8, 4}) {
+        if (st != AT_OK) break;
+        const int v = std::abs(k) >= 16 ? 1 : (k == 8 ? 2 : 3);
         st = at_batch_set_variant(b, v);
+        bool ok = true;
+        for (const Derived &d : b->d) ok = ok && d.W % std::abs(k) == 0 && fused_shape(d, 1, k).ok;
+        if (!ok) continue;
+        b->kind = k;
         // largest steps per launch first: a smaller count must be 2% faster to
         // replace it (fewer launches, and fewer launch tails, on a near tie)
         for (int ci = (int)(sizeof(cands) / sizeof(cands[0])) - 1; ci >= 0; --ci) {
             const int s = cands[ci];
             if (st != AT_OK) break;
-            if (s > b->max_fuse) continue;
+            b->fuse = s;
+            if (s > b->max_fuse || batch_fuse(b) != s) continue;
             float ms_best = 1e30f;
+            const int steps = trial_length(trial_steps, s, b->nsteps_max);
             for (int rep = 0; rep < 2 && st == AT_OK; ++rep) {
                 st = at_batch_reset(b);
                 hipError_t e = hipSuccess;
@@ -1607,19 +1761,20 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
                     e = launch_copy(t1[j], u0[j], b->d[j].N, b->st);
                 b->fuse = s;
                 if (st == AT_OK && e == hipSuccess) e = hipEventRecord(e0, b->st);
-                if (st == AT_OK && e == hipSuccess) st = at_batch_run(b, t1, t2, trial_steps, 0);
+                if (st == AT_OK && e == hipSuccess) st = at_batch_run(b, t1, t2, steps, 0);
                 if (st == AT_OK && e == hipSuccess) e = hipEventRecord(e1, b->st);
                 if (st == AT_OK && e == hipSuccess) e = hipEventSynchronize(e1);
                 float ms = 0.f;
                 if (st == AT_OK && e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
                 if (e != hipSuccess && st == AT_OK)
                     st = fail(AT_ERR_HIP, "at_batch_autotune: %s", hipGetErrorString(e));
-                ms_best = std::min(ms_best, ms);
+                ms_best = std::min(ms_best, ms / (float)steps);
             }
             if (st == AT_OK && ms_best < best_ms * 0.98f) {
                 best_ms = ms_best;
                 best_s = s;
                 best_v = v;
+                best_k = k;
             }
         }
     }
@@ -1628,6 +1783,7 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
     if (st) { b->n = 0; return st; }
     st = at_batch_set_variant(b, best_v);
     if (st) return st;
+    b->kind = best_k;
     st = at_batch_reset(b);
     if (st) return st;
     AT_HIP(hipStreamSynchronize(b->st));

@@ -26,10 +26,13 @@ struct Step1D {
     int32_t stale;            // 1: halo = level n-k without extrapolation
     int32_t publish;          // ring writes of level edges: 0 none, 1 every level,
                               // 2 the last D levels of the launch (1D)
-    int32_t RL;               // left rim of the loaded region (aligned kernel)
+    int32_t RL;               // left rim of the loaded region (one-step kernel)
     int32_t slot0;            // n0 mod R (ring slot of level n0)
     int32_t D;                // delayed levels below n0 a step may read: L + m - 1
-    double *levels;           // optional: levels n0+1 .. n0+s-1 stored at levels + t*N (aligned kernel)
+    double *levels;           // optional: levels n0+1 .. n0+s-1 stored at levels + t*N (fused kernels)
+    // fused regions (at_wave1d.h), in threads
+    int32_t tpt, nf;          // threads per tile; those with all their points
+    int32_t CT, RT;           // threads owned by a region; rim threads on each side
     double nu, dt, c1, c2, cadv;
     double A1, A2;            // contracted mode: dt*c1, dt*(nu*c2)
 };
@@ -118,17 +121,20 @@ hipError_t launch_delays(int8_t *out, int64_t nsteps, int64_t F, int L, int m, i
 hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t st);
 hipError_t launch_poison(double *ring, int64_t R, int64_t lev, int s0, int nlive, hipStream_t st);
 hipError_t launch_copy(double *dst, const double *src, int64_t n, hipStream_t st);
-size_t step1d_lds_bytes(int order, int s, int NT, int D, int ppt, bool dense);
+size_t step1d_lds_bytes(int order, int s, int NT, int D, int ppt);
 int step1d_points_per_thread();
 int step1d_plain_points_per_thread();
-hipError_t launch_step1d(const Step1D &a, int order, bool linear, bool aligned, bool fma, int ppt,
+hipError_t launch_step1d(const Step1D &a, int order, bool linear, bool plain, bool fma,
                          int64_t nblocks, hipStream_t st);
 size_t step1d_whole_lds_bytes(int order, int64_t P, int D);
 int step1d_whole_ppt(int64_t N, int64_t W, int64_t P, int order, int D);
 hipError_t launch_step1d_whole(const Step1D &a, int order, bool linear, bool fma, int ppt,
                                hipStream_t st);
-hipError_t launch_step1d_batch(const Step1D *descs, const int2 *tbl, int64_t nblocks, int order,
-                               bool linear, bool fma, int ppt, int64_t n0, int flip, size_t lds,
+size_t wave1d_lds_bytes(int order, int s, int NT, int D, int ppt, int nw);
+hipError_t launch_wave1d(const Step1D &a, int order, bool linear, bool fma, int ppt, int nw,
+                         int64_t nblocks, hipStream_t st);
+hipError_t launch_wave1d_batch(const Step1D *descs, const int2 *tbl, int64_t nblocks, int order,
+                               bool linear, bool fma, int ppt, int nw, int64_t n0, int flip, size_t lds,
                                hipStream_t st);
 hipError_t launch_adj1d(const Adj1D &a, int order, bool linear, int64_t nblocks,
                         hipStream_t st);

@@ -13,7 +13,7 @@
 // levels (D = L + m - 1, the deepest level a step reads below its own).
 // Every thread's points lie in one tile (the tile width is a multiple of
 // PPT), so the AT values are written into the halo slots of a thread's
-// register window before the standard stencil, as in the aligned kernels.
+// register window before the standard stencil, as in the fused kernels.
 #include "at_internal.h"
 #include "at_stencil1d.h"
 
