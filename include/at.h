@@ -225,11 +225,11 @@ at_status at_autotune(at_ctx *ctx, const double *u0, double *t1, double *t2,
                       int32_t trial_steps, int32_t *chosen);
 
 /* Kernel variant of a 3D context (results are bit-identical for every
- * variant; at_autotune picks one for 3D contexts): 0..5 LDS-tiled with
- * per-point halos (tile rows, prefetch depth, register budget), 6..8 and
- * 12..14 LDS-tiled with halos in the tile rims and 1 to 4 planes prefetched
- * (block widths multiples of the tile, AT_ERR_ARG otherwise), 9..11
- * barrier-free column march, 15 and 16 two steps per launch (levels n ->
+ * variant; at_autotune picks one for 3D contexts): 0..5 and 9..11
+ * any block widths (one kernel; 0..5 keep an upper bound on the scalars),
+ * 6..8 and 12..14 LDS-tiled with halos in the tile rims and 1 to 4 planes
+ * prefetched (block widths multiples of the tile, AT_ERR_ARG otherwise), 15
+ * and 16 two steps per launch (levels n ->
  * n+2 in one z-march of 64 x 8 or 64 x 4 tiles: each workgroup recomputes
  * level n+1 on a one-point rim around its tile as the neighbouring block
  * would, and takes it from the ring's AT levels where the step-(n+1) delay

@@ -487,6 +487,7 @@ at_status at3_publish(at_ctx *c, const double *u, int64_t n);
 int at3_max_fuse(const at_ctx *c);
 int at3_variants();
 bool at3_variant_ok(const at_config *c, int var);
+bool at3_is_aligned(int var);
 bool at3_is_fused(int var);
 int at3_single_variant(const at_config *c, int var);
 int64_t at3_ws_capacity(const at_config *c);
@@ -1056,7 +1057,8 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
         if (whole_ppt(c) != 0) cands.push_back({-kWholeVariant, 0});   // one launch per run
     } else {
         for (int v = 0; v < at3_variants(); ++v)
-            if (at3_variant_ok(&c->cfg, v)) cands.push_back({v, at3_is_fused(v) ? 2 : 1});
+            if (at3_variant_ok(&c->cfg, v) && (at3_is_aligned(v) || at3_is_fused(v) || cands.empty()))
+                cands.push_back({v, at3_is_fused(v) ? 2 : 1});   // (the others are one kernel)
     }
     hipEvent_t e0, e1;
     AT_HIP(hipEventCreate(&e0));

@@ -20,13 +20,10 @@
 // faces x-low, x-high, y-low, y-high, z-low, z-high, each [NC][plane] with the
 // plane indexed (z, y) for x-faces, (z, x) for y-faces, (y, x) for z-faces.
 //
-// Work decomposition (2.5D): a workgroup of 64 x 8 threads owns a 64 x 8 x-y
-// tile (one point per thread) and marches through ZC planes in z.  Each
-// thread keeps the z-1, z, z+1 values (NC components) in registers and has
-// planes z+2 and z+3 in flight; the current plane with one-point rims sits in a
-// double-buffered LDS tile for the x and y neighbours (one barrier per
-// plane).  Block faces inside the tile are handled per point (any block
-// width >= 2).
+// Work decomposition: blocks that are multiples of a 64 x 8 x-y tile march it
+// through z (k_step3d_aligned, 2.5D: the planes z-1 .. z+2 in registers, the
+// current plane with one-point rims in a double-buffered LDS tile); any other
+// block widths run one thread per point (k_step3d_point).
 #include "../../include/at.h"
 #include "at_internal.h"
 #include "at_ws.h"
@@ -75,191 +72,171 @@ constexpr int waves_for(int minw, int nc) { return nc <= 5 ? minw : (minw * 3 / 
 
 __device__ __forceinline__ int wrap32(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
-// TY rows per tile (= waves per workgroup, one row per thread); PF planes
-// prefetched ahead (1 or 2); MINW waves per SIMD the register budget allows.
-template <int TY, int PF, int MINW, int NC>
-__global__ __launch_bounds__(TX * TY, waves_for(MINW, NC)) void k_step3d(Step3D A)
+// AT value H = v0 + k (v0 - v1) (Eq. (1), m = 2); the raw value when k = 0
+// and the level n-k value itself in the stale-halo mode
+__device__ __forceinline__ double at_h(int k, bool stale, double v0, double v1)
 {
-    __shared__ double pl[2][NC][TY + 2][TX + 2];
-    const int tx = threadIdx.x, ty = threadIdx.y;
-    const int nx = (int)A.nx, ny = (int)A.ny, nz = (int)A.nz;
-    const int X0 = blockIdx.x * TX, Y0 = blockIdx.y * TY;
-    const int Z0 = blockIdx.z * A.ZC;
-    const int Z1 = (Z0 + A.ZC < nz) ? Z0 + A.ZC : nz;
-    const int wx = (nx - X0 < TX) ? nx - X0 : TX;
-    const int hy = (ny - Y0 < TY) ? ny - Y0 : TY;
-    const int x = X0 + tx, y = Y0 + ty;
-    const bool act = tx < wx && ty < hy;
-    const int plane = nx * ny;
-    const int bx = x / A.Wx, lx = x - bx * A.Wx;
-    const int by = y / A.Wy, ly = y - by * A.Wy;
-    const double *U0 = A.uin;
-    const int64_t npt = A.npt;
-    // rim loads of this thread (lanes 0/1: x rims of its row; waves 0/1: y rims)
-    const bool xrim = tx < 2 && ty < hy;
-    const int xs = tx == 0 ? wrap32(X0 - 1, nx) : wrap32(X0 + wx, nx);
-    const int xcol = tx == 0 ? 0 : wx + 1;
-    const bool yrim = ty < 2 && tx < wx;
-    const int ys = ty == 0 ? wrap32(Y0 - 1, ny) : wrap32(Y0 + hy, ny);
-    const int yrow = ty == 0 ? 0 : hy + 1;
-    const int col = y * nx + x;
+    return (k > 0 && !stale) ? v0 + (double)k * (v0 - v1) : v0;
+}
 
-    auto ld3 = [&](int off, double *v, bool on) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) v[c] = on ? U0[c * npt + off] : 0.0;
-    };
-    // register pipeline: planes z-1, z, z+1 in use, z+2 (and z+3 when PF = 2)
-    // in flight; rims of plane z+1 (and z+2) in flight
-    double zm[NC], zc[NC], zp[NC], zq[NC], zr[NC], rx[NC], ry[NC], rx2[NC], ry2[NC];
-    ld3(wrap32(Z0 - 1, nz) * plane + col, zm, act);
-    ld3(Z0 * plane + col, zc, act);
-    ld3(wrap32(Z0 + 1, nz) * plane + col, zp, act);
-    if (PF == 2) ld3(wrap32(Z0 + 2, nz) * plane + col, zq, act && Z0 + 1 < Z1);
-    ld3(Z0 * plane + y * nx + xs, rx, xrim);
-    ld3(Z0 * plane + ys * nx + x, ry, yrim);
-    // plane Z0 into buffer 0
+// Quotient of n < 2^31 by a divisor d >= 2 (Granlund and Montgomery 1994): with
+// s = ceil(log2 d) and mul = ceil(2^(31+s) / d), floor(n / d) =
+// floor(n * mul / 2^(31+s))
+struct Div31 {
+    uint32_t mul, shift;      // shift = s - 1
+};
+
+__device__ __forceinline__ unsigned div31(unsigned n, Div31 d) { return __umulhi(n, d.mul) >> d.shift; }
+
+Div31 make_div31(uint32_t d)
+{
+    uint32_t s = 1;
+    while (((uint64_t)1 << s) < d) ++s;
+    const unsigned __int128 num = (unsigned __int128)1 << (31 + s);
+    return Div31{(uint32_t)((num + d - 1) / d), s - 1};
+}
+
+// The work order of k_step3d_point
+struct Point3D {
+    uint32_t total, per;      // workgroups; an XCD's share of them
+    uint32_t strip_wgs, plane_wgs;   // of a strip; of one plane of a strip
+    int32_t rows;             // rows of a strip
+    Div31 dnx, dWx, dWy;
+};
+
+constexpr int kPointThreads = 256;
+
+// Any block widths: one thread per point, every neighbour straight from the
+// field (L1/L2 serve the re-reads), the AT halo values of the up to three faces
+// a point lies on (one per axis) from the ring where its delay is positive.
+// What bounds it is latency and the L2s' bandwidth: with a thread per point a
+// launch has all its waves in flight (a march through z gives a 120^3 grid 480
+// workgroups that walk 15 planes one after another), and each wave has two
+// dependent trips to memory, delays then ring, whichever faces its lanes touch.
+// Work order: a workgroup takes 256 points of one plane of a strip of rows; the
+// workgroups of a strip follow each other along z, and each XCD (workgroups are
+// dealt to the 8 of them in turn) takes a contiguous eighth of that order, so
+// that the planes z - 1 .. z + 1 of a strip are in its own L2 when they are
+// read again.  120^3 points in blocks of 12^3 (us per step): 96 marching, 50
+// this way.
+template <int NC>
+__global__ __launch_bounds__(kPointThreads) void k_step3d_point(Step3D A, Point3D G)
+{
+    const int nx = (int)A.nx, ny = (int)A.ny, nz = (int)A.nz;
+    // ---- this workgroup's place in the order, its plane and strip (uniform)
+    const unsigned wid = (blockIdx.x % 8) * G.per + blockIdx.x / 8;
+    if (wid >= G.total) return;
+    const unsigned strip = wid / G.strip_wgs, in_strip = wid - strip * G.strip_wgs;
+    const int z = (int)(in_strip / G.plane_wgs);
+    const int Y0 = (int)strip * G.rows;
+    const int rows = ny - Y0 < G.rows ? ny - Y0 : G.rows;
+    const unsigned idx = (in_strip - (unsigned)z * G.plane_wgs) * kPointThreads + threadIdx.x;
+    if (idx >= (unsigned)rows * (unsigned)nx) return;
+    const int yr = (int)div31(idx, G.dnx);
+    const int x = (int)idx - yr * nx, y = Y0 + yr;
+    const int bx = (int)div31((unsigned)x, G.dWx), by = (int)div31((unsigned)y, G.dWy);
+    const int lx = x - bx * A.Wx, ly = y - by * A.Wy;
+    const int bz = z / A.Wz, lz = z - bz * A.Wz;
+    const bool xl = lx == 0, xh = lx == A.Wx - 1, yl = ly == 0, yh = ly == A.Wy - 1;
+    const bool zl = lz == 0, zh = lz == A.Wz - 1;
+    // ---- delays of the faces this point lies on (block widths are at least 2)
+    const int64_t b = ((int64_t)bz * A.Py + by) * A.Px + bx;
+    const int8_t *krow = A.delays + A.n * A.F + 6 * b;
+    int kx = 0, ky = 0, kz = 0;
+    if (xl || xh) kx = krow[xl ? 0 : 1];
+    if (yl || yh) ky = krow[yl ? 2 : 3];
+    if (zl || zh) kz = krow[zl ? 4 : 5];
+    // ---- the point and its raw neighbours
+    const int64_t plane = (int64_t)nx * ny;
+    const double *U = A.uin + z * plane;
+    const int at = y * nx + x;
+    const int oxl = x == 0 ? at + nx - 1 : at - 1, oxh = x == nx - 1 ? at - (nx - 1) : at + 1;
+    const int oyl = y == 0 ? at + (ny - 1) * nx : at - nx;
+    const int oyh = y == ny - 1 ? at - (ny - 1) * nx : at + nx;
+    const int64_t dzl = z == 0 ? (nz - 1) * plane : -plane, dzh = z == nz - 1 ? -(nz - 1) * plane : plane;
+    double u[NC], nb[6][NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        if (act) pl[0][c][ty + 1][tx + 1] = zc[c];
-        if (xrim) pl[0][c][ty + 1][xcol] = rx[c];
-        if (yrim) pl[0][c][yrow][tx + 1] = ry[c];
+        const double *p = U + c * A.npt;
+        u[c] = p[at];
+        nb[0][c] = p[oxl];
+        nb[1][c] = p[oxh];
+        nb[2][c] = p[oyl];
+        nb[3][c] = p[oyh];
+        nb[4][c] = p[at + dzl];
+        nb[5][c] = p[at + dzh];
     }
-    {   // rims of plane Z0 + 1 (and Z0 + 2)
-        const int zo = wrap32(Z0 + 1, nz) * plane;
-        ld3(zo + y * nx + xs, rx, xrim && Z0 + 1 < Z1);
-        ld3(zo + ys * nx + x, ry, yrim && Z0 + 1 < Z1);
-        if (PF == 2) {
-            const int zo2 = wrap32(Z0 + 2, nz) * plane;
-            ld3(zo2 + y * nx + xs, rx2, xrim && Z0 + 2 < Z1);
-            ld3(zo2 + ys * nx + x, ry2, yrim && Z0 + 2 < Z1);
+    // ---- AT halo values (section 2, Eq. (1)): the facing face of the block
+    // across, levels n-k and n-k-1; the loads of all axes go out before the
+    // first is used
+    const int px = lz * A.Wy + ly, py = lz * A.Wx + lx, pz = ly * A.Wx + lx;
+    double v0[3][NC], v1[3][NC];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int k = a == 0 ? kx : (a == 1 ? ky : kz);
+        if (k > 0) {
+            const bool lo = a == 0 ? xl : (a == 1 ? yl : zl);
+            int n0 = bx, n1 = by, n2 = bz;
+            if (a == 0) n0 = wrap32(bx + (lo ? -1 : 1), A.Px);
+            else if (a == 1) n1 = wrap32(by + (lo ? -1 : 1), A.Py);
+            else n2 = wrap32(bz + (lo ? -1 : 1), A.Pz);
+            const int pos = a == 0 ? px : (a == 1 ? py : pz);
+            const int64_t off = (((int64_t)n2 * A.Py + n1) * A.Px + n0) * A.bstride +
+                                (lo ? A.foff[2 * a + 1] : A.foff[2 * a]) + pos;
+            int s0 = A.slot0 - k;
+            if (s0 < 0) s0 += A.R;
+            int s1 = s0 - 1;
+            if (s1 < 0) s1 += A.R;
+            const double *r0 = A.ring + s0 * A.level + off;
+            const double *r1 = A.stale ? r0 : A.ring + s1 * A.level + off;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                v0[a][c] = r0[c * A.psz[a]];
+                v1[a][c] = r1[c * A.psz[a]];
+            }
         }
     }
-    const int8_t *krow = A.delays + A.n * A.F;
-    const int64_t slot = A.slot0 + 1 == A.R ? 0 : A.slot0 + 1;   // level n+1 is published
-
-    int bz = Z0 / A.Wz, lz = Z0 - bz * A.Wz;
-    int kbz = -1, kc[6] = {0, 0, 0, 0, 0, 0};
-    for (int z = Z0; z < Z1; ++z, ++lz) {
-        if (lz == A.Wz) { lz = 0; ++bz; }
-        const int buf = (z - Z0) & 1;
-        const bool more = z + 1 < Z1;
-        if (PF == 2) ld3(wrap32(z + 3, nz) * plane + col, zr, act && z + 2 < Z1);
-        else ld3(wrap32(z + 2, nz) * plane + col, zq, act && more);
-        __syncthreads();
-        if (act) {
-            const int64_t b = ((int64_t)bz * A.Py + by) * A.Px + bx;
-            if (bz != kbz) {          // face delays of this block: reloaded only at block changes
-                kbz = bz;
-                kc[0] = lx == 0 ? krow[6 * b + 0] : 0;
-                kc[1] = lx == A.Wx - 1 ? krow[6 * b + 1] : 0;
-                kc[2] = ly == 0 ? krow[6 * b + 2] : 0;
-                kc[3] = ly == A.Wy - 1 ? krow[6 * b + 3] : 0;
-                kc[4] = krow[6 * b + 4];
-                kc[5] = krow[6 * b + 5];
-            }
-            const int kxl = kc[0], kxh = kc[1], kyl = kc[2], kyh = kc[3];
-            const int kzl = lz == 0 ? kc[4] : 0;
-            const int kzh = lz == A.Wz - 1 ? kc[5] : 0;
-            const int px = lz * A.Wy + ly, py = lz * A.Wx + lx, pz = ly * A.Wx + lx;
-            // neighbours: x/y from the LDS tile, z from registers
-            double nb[6][NC];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const int k = a == 0 ? kx : (a == 1 ? ky : kz);
+        if (k > 0) {
+            const bool lo = a == 0 ? xl : (a == 1 ? yl : zl);
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                nb[0][c] = pl[buf][c][ty + 1][tx];
-                nb[1][c] = pl[buf][c][ty + 1][tx + 2];
-                nb[2][c] = pl[buf][c][ty][tx + 1];
-                nb[3][c] = pl[buf][c][ty + 2][tx + 1];
-                nb[4][c] = zm[c];
-                nb[5][c] = zp[c];
-            }
-            // AT halo values across the block faces this point touches
-            const int kf[6] = {kxl, kxh, kyl, kyh, kzl, kzh};
-#pragma unroll
-            for (int f = 0; f < 6; ++f) {
-                const int kk = kf[f];
-                if (kk > 0) {
-                    const int a = f >> 1, sd = f & 1;
-                    int n0 = bx, n1 = by, n2 = bz;
-                    if (a == 0) n0 = wrap32(bx + (sd ? 1 : -1), A.Px);
-                    else if (a == 1) n1 = wrap32(by + (sd ? 1 : -1), A.Py);
-                    else n2 = wrap32(bz + (sd ? 1 : -1), A.Pz);
-                    const int pos = a == 0 ? px : (a == 1 ? py : pz);
-                    const int64_t off = (((int64_t)n2 * A.Py + n1) * A.Px + n0) * A.bstride +
-                                        A.foff[2 * a + (1 - sd)] + pos;
-                    int s0 = A.slot0 - kk, s1 = A.slot0 - kk - 1;     // levels n-k, n-k-1
-                    if (s0 < 0) s0 += A.R;
-                    if (s1 < 0) s1 += A.R;
-                    const double *r0 = A.ring + s0 * A.level + off;
-                    const double *r1 = A.ring + s1 * A.level + off;
-                    const double dk = (double)kk;
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        const double v0 = r0[c * A.psz[a]];
-                        nb[f][c] = A.stale ? v0 : v0 + dk * (v0 - r1[c * A.psz[a]]);
-                    }
-                }
-            }
-            const double ux = zc[0], uy = zc[1], uz = zc[2];
-            double *out = A.uout + (int64_t)z * plane + col;
-            double ov[NC];
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const double u = zc[c];
-                const double xl = nb[0][c], xr = nb[1][c], yl = nb[2][c], yh = nb[3][c];
-                const double zl = nb[4][c], zh = nb[5][c];
-                const double D1x = (xr - xl) * A.c1[0], D2x = ((xr - 2.0 * u) + xl) * A.c2[0];
-                const double D1y = (yh - yl) * A.c1[1], D2y = ((yh - 2.0 * u) + yl) * A.c2[1];
-                const double D1z = (zh - zl) * A.c1[2], D2z = ((zh - 2.0 * u) + zl) * A.c2[2];
-                const double lap = (D2x + D2y) + D2z;
-                const double adv = (ux * D1x + uy * D1y) + uz * D1z;
-                ov[c] = u + A.dt * (A.kappa[c] * lap - adv);
-                out[c * A.npt] = ov[c];
-            }
-            // publish the level-(n+1) values of points on block faces
-            const bool onface = lx == 0 || lx == A.Wx - 1 || ly == 0 || ly == A.Wy - 1 ||
-                                lz == 0 || lz == A.Wz - 1;
-            if (A.publish && onface) {
-                double *base = A.ring + slot * A.level + b * A.bstride;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const double u = ov[c];
-                    if (lx == 0) base[A.foff[0] + c * A.psz[0] + px] = u;
-                    if (lx == A.Wx - 1) base[A.foff[1] + c * A.psz[0] + px] = u;
-                    if (ly == 0) base[A.foff[2] + c * A.psz[1] + py] = u;
-                    if (ly == A.Wy - 1) base[A.foff[3] + c * A.psz[1] + py] = u;
-                    if (lz == 0) base[A.foff[4] + c * A.psz[2] + pz] = u;
-                    if (lz == A.Wz - 1) base[A.foff[5] + c * A.psz[2] + pz] = u;
-                }
+                const double h = at_h(k, A.stale != 0, v0[a][c], v1[a][c]);
+                if (lo) nb[2 * a][c] = h;
+                else nb[2 * a + 1][c] = h;
             }
         }
-        if (more) {
-            // plane z+1 into the other buffer (its readers finished before the barrier)
+    }
+    double *out = A.uout + z * plane + at;
+    double ov[NC];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                if (act) pl[buf ^ 1][c][ty + 1][tx + 1] = zp[c];
-                if (xrim) pl[buf ^ 1][c][ty + 1][xcol] = rx[c];
-                if (yrim) pl[buf ^ 1][c][yrow][tx + 1] = ry[c];
-            }
-            if (PF == 2) {                                            // rims of plane z+3
-                const int zo = wrap32(z + 3, nz) * plane;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) { rx[c] = rx2[c]; ry[c] = ry2[c]; }
-                ld3(zo + y * nx + xs, rx2, xrim && z + 3 < Z1);
-                ld3(zo + ys * nx + x, ry2, yrim && z + 3 < Z1);
-            } else {                                                  // rims of plane z+2
-                const int zo = wrap32(z + 2, nz) * plane;
-                ld3(zo + y * nx + xs, rx, xrim && z + 2 < Z1);
-                ld3(zo + ys * nx + x, ry, yrim && z + 2 < Z1);
-            }
-        }
+    for (int c = 0; c < NC; ++c) {
+        const double w = u[c];
+        const double D1x = (nb[1][c] - nb[0][c]) * A.c1[0];
+        const double D2x = ((nb[1][c] - 2.0 * w) + nb[0][c]) * A.c2[0];
+        const double D1y = (nb[3][c] - nb[2][c]) * A.c1[1];
+        const double D2y = ((nb[3][c] - 2.0 * w) + nb[2][c]) * A.c2[1];
+        const double D1z = (nb[5][c] - nb[4][c]) * A.c1[2];
+        const double D2z = ((nb[5][c] - 2.0 * w) + nb[4][c]) * A.c2[2];
+        const double lap = (D2x + D2y) + D2z;
+        const double adv = (u[0] * D1x + u[1] * D1y) + u[2] * D1z;
+        ov[c] = w + A.dt * (A.kappa[c] * lap - adv);
+        out[c * A.npt] = ov[c];
+    }
+    // ---- publish the level-(n+1) values of points on block faces
+    if (A.publish && (xl || xh || yl || yh || zl || zh)) {
+        const int64_t slot = A.slot0 + 1 == A.R ? 0 : A.slot0 + 1;
+        double *base = A.ring + slot * A.level + b * A.bstride;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-            zm[c] = zc[c]; zc[c] = zp[c]; zp[c] = zq[c];
-            if (PF == 2) zq[c] = zr[c];
+            if (xl || xh) base[(xl ? A.foff[0] : A.foff[1]) + c * A.psz[0] + px] = ov[c];
+            if (yl || yh) base[(yl ? A.foff[2] : A.foff[3]) + c * A.psz[1] + py] = ov[c];
+            if (zl || zh) base[(zl ? A.foff[4] : A.foff[5]) + c * A.psz[2] + pz] = ov[c];
         }
     }
 }
-
 
 // One neighbour value of all NC components for a tile rim or a z face.
 // Across a block face it comes from the ring: levels n-k and n-k-1 of the
@@ -290,13 +267,6 @@ __device__ __forceinline__ NbC<NC> load_nbc(const double *ring, const double *fi
 #pragma unroll
     for (int c = 0; c < NC; ++c) r.b[c] = COH ? ld_coherent(p1 + c * cs) : p1[c * cs];
     return r;
-}
-
-// AT value H = v0 + k (v0 - v1) (Eq. (1), m = 2); the raw value when k = 0
-// and the level n-k value itself in the stale-halo mode
-__device__ __forceinline__ double at_h(int k, bool stale, double v0, double v1)
-{
-    return (k > 0 && !stale) ? v0 + (double)k * (v0 - v1) : v0;
 }
 
 // Aligned variant: block widths are multiples of the tile (Wx % 64 == 0,
@@ -1040,128 +1010,6 @@ __global__ __launch_bounds__(TX * kWsTY, 4) void k_ws3d(Step3D A, Ws3D W)
     }
 }
 
-// Barrier-free variant: every thread marches its (x, y) column through the
-// z range with the z-1, z, z+1 values in registers (plane z+2 in flight) and
-// reads its x and y neighbours straight from global memory (L1/L2 hits: the
-// same rows are the neighbouring threads' own loads).  No LDS, no barrier, so
-// each wave advances on its own and many loads are in flight per wave.
-template <int TY, int NC>
-__global__ __launch_bounds__(TX * TY) void k_step3d_direct(Step3D A)
-{
-    const int tx = threadIdx.x, ty = threadIdx.y;
-    const int nx = (int)A.nx, ny = (int)A.ny, nz = (int)A.nz;
-    const int X0 = blockIdx.x * TX, Y0 = blockIdx.y * TY;
-    const int Z0 = blockIdx.z * A.ZC;
-    const int Z1 = (Z0 + A.ZC < nz) ? Z0 + A.ZC : nz;
-    const int x = X0 + tx, y = Y0 + ty;
-    if (x >= nx || y >= ny) return;            // no barrier below: idle threads may leave
-    const int plane = nx * ny;
-    const int col = y * nx + x;
-    const int xm = (x == 0 ? nx : x) - 1, xp = (x + 1 == nx ? 0 : x + 1);
-    const int ym = (y == 0 ? ny : y) - 1, yp = (y + 1 == ny ? 0 : y + 1);
-    const int bx = x / A.Wx, lx = x - bx * A.Wx;
-    const int by = y / A.Wy, ly = y - by * A.Wy;
-    const double *U0 = A.uin;
-    auto U = [&](int c, int off) -> double { return U0[(int64_t)c * A.npt + off]; };
-    double zm[NC], zc[NC], zp[NC], zq[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        zm[c] = U(c, wrap32(Z0 - 1, nz) * plane + col);
-        zc[c] = U(c, Z0 * plane + col);
-        zp[c] = U(c, wrap32(Z0 + 1, nz) * plane + col);
-    }
-    const int8_t *krow = A.delays + A.n * A.F;
-    const int64_t slot = A.slot0 + 1 == A.R ? 0 : A.slot0 + 1;   // level n+1 is published
-    int bz = Z0 / A.Wz, lz = Z0 - bz * A.Wz;
-    int kbz = -1, kc[6] = {0, 0, 0, 0, 0, 0};
-    for (int z = Z0; z < Z1; ++z, ++lz) {
-        if (lz == A.Wz) { lz = 0; ++bz; }
-        const bool more = z + 1 < Z1;
-        const int po = z * plane;
-        double nb[6][NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            zq[c] = more ? U(c, wrap32(z + 2, nz) * plane + col) : 0.0;
-            nb[0][c] = U(c, po + y * nx + xm);
-            nb[1][c] = U(c, po + y * nx + xp);
-            nb[2][c] = U(c, po + ym * nx + x);
-            nb[3][c] = U(c, po + yp * nx + x);
-            nb[4][c] = zm[c];
-            nb[5][c] = zp[c];
-        }
-        const int64_t b = ((int64_t)bz * A.Py + by) * A.Px + bx;
-        if (bz != kbz) {              // face delays of this block: reloaded only at block changes
-            kbz = bz;
-            kc[0] = lx == 0 ? krow[6 * b + 0] : 0;
-            kc[1] = lx == A.Wx - 1 ? krow[6 * b + 1] : 0;
-            kc[2] = ly == 0 ? krow[6 * b + 2] : 0;
-            kc[3] = ly == A.Wy - 1 ? krow[6 * b + 3] : 0;
-            kc[4] = krow[6 * b + 4];
-            kc[5] = krow[6 * b + 5];
-        }
-        const int kf[6] = {kc[0], kc[1], kc[2], kc[3], lz == 0 ? kc[4] : 0,
-                           lz == A.Wz - 1 ? kc[5] : 0};
-        const int px = lz * A.Wy + ly, py = lz * A.Wx + lx, pz = ly * A.Wx + lx;
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            const int kk = kf[f];
-            if (kk > 0) {
-                const int a = f >> 1, sd = f & 1;
-                int n0 = bx, n1 = by, n2 = bz;
-                if (a == 0) n0 = wrap32(bx + (sd ? 1 : -1), A.Px);
-                else if (a == 1) n1 = wrap32(by + (sd ? 1 : -1), A.Py);
-                else n2 = wrap32(bz + (sd ? 1 : -1), A.Pz);
-                const int pos = a == 0 ? px : (a == 1 ? py : pz);
-                const int64_t off = (((int64_t)n2 * A.Py + n1) * A.Px + n0) * A.bstride +
-                                    A.foff[2 * a + (1 - sd)] + pos;
-                int s0 = A.slot0 - kk, s1 = A.slot0 - kk - 1;
-                if (s0 < 0) s0 += A.R;
-                if (s1 < 0) s1 += A.R;
-                const double *r0 = A.ring + s0 * A.level + off;
-                const double *r1 = A.ring + s1 * A.level + off;
-                const double dk = (double)kk;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const double v0 = r0[c * A.psz[a]];
-                    nb[f][c] = A.stale ? v0 : v0 + dk * (v0 - r1[c * A.psz[a]]);
-                }
-            }
-        }
-        const double ux = zc[0], uy = zc[1], uz = zc[2];
-        double *out = A.uout + (int64_t)po + col;
-        double ov[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const double u = zc[c];
-            const double xl = nb[0][c], xr = nb[1][c], yl = nb[2][c], yh = nb[3][c];
-            const double zl = nb[4][c], zh = nb[5][c];
-            const double D1x = (xr - xl) * A.c1[0], D2x = ((xr - 2.0 * u) + xl) * A.c2[0];
-            const double D1y = (yh - yl) * A.c1[1], D2y = ((yh - 2.0 * u) + yl) * A.c2[1];
-            const double D1z = (zh - zl) * A.c1[2], D2z = ((zh - 2.0 * u) + zl) * A.c2[2];
-            const double lap = (D2x + D2y) + D2z;
-            const double adv = (ux * D1x + uy * D1y) + uz * D1z;
-            ov[c] = u + A.dt * (A.kappa[c] * lap - adv);
-            out[c * A.npt] = ov[c];
-        }
-        if (A.publish && (lx == 0 || lx == A.Wx - 1 || ly == 0 || ly == A.Wy - 1 || lz == 0 ||
-                          lz == A.Wz - 1)) {
-            double *base = A.ring + slot * A.level + b * A.bstride;
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const double u = ov[c];
-                if (lx == 0) base[A.foff[0] + c * A.psz[0] + px] = u;
-                if (lx == A.Wx - 1) base[A.foff[1] + c * A.psz[0] + px] = u;
-                if (ly == 0) base[A.foff[2] + c * A.psz[1] + py] = u;
-                if (ly == A.Wy - 1) base[A.foff[3] + c * A.psz[1] + py] = u;
-                if (lz == 0) base[A.foff[4] + c * A.psz[2] + pz] = u;
-                if (lz == A.Wz - 1) base[A.foff[5] + c * A.psz[2] + pz] = u;
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < NC; ++c) { zm[c] = zc[c]; zc[c] = zp[c]; zp[c] = zq[c]; }
-    }
-}
-
 // Level n's block-face values from the field into ring slot n mod R (the
 // steps read the faces of the current level from the ring; a run starts by
 // publishing them once)
@@ -1237,7 +1085,8 @@ uint64_t at3_ring_level_doubles(const at_config *c)
 }
 
 // kernel variants the autotuner may choose from (tile rows, prefetch depth,
-// register budget); every variant performs the same operations.  Variants
+// register budget); every variant performs the same operations.  0 to 5 and 9
+// to 11 are k_step3d_point, 6 to 8 and 12 to 14 k_step3d_aligned.  Variants
 // 15 and 16 advance two steps per launch (k_step3d_f2 with 8 and 4 tile rows).
 int at3_variants() { return 17; }
 static int k3_rows(int var)
@@ -1245,8 +1094,7 @@ static int k3_rows(int var)
     static const int r[17] = {8, 8, 4, 4, 16, 16, 8, 16, 4, 4, 8, 16, 8, 8, 16, 8, 4};
     return r[var < 0 || var > 16 ? 0 : var];
 }
-static bool is_direct(int var) { return var >= 9 && var <= 11; }
-static bool is_aligned(int var) { return (var >= 6 && var <= 8) || (var >= 12 && var <= 14); }
+bool at3_is_aligned(int var) { return (var >= 6 && var <= 8) || (var >= 12 && var <= 14); }
 bool at3_is_fused(int var) { return var == 15 || var == 16; }
 
 // LDS of the two-step kernel for TY rows and NC components (0: no build)
@@ -1283,8 +1131,9 @@ bool at3_variant_ok(const at_config *c, int var)
         const size_t lds = f2_lds_bytes(k3_rows(var), nc);
         return lds > 0 && lds <= kMaxLds && Wx % TX == 0 && Wy % k3_rows(var) == 0 && Wz >= 2;
     }
-    if (!is_direct(var) && tile_lds(k3_rows(var), nc) > kMaxLds) return false;
-    if (!is_aligned(var)) return true;
+    // the former tiled variants keep the limits they had
+    if (!(var >= 9 && var <= 11) && tile_lds(k3_rows(var), nc) > kMaxLds) return false;
+    if (!at3_is_aligned(var)) return true;
     return Wx % TX == 0 && Wy % k3_rows(var) == 0;
 }
 
@@ -1429,21 +1278,12 @@ static bool launch3(int var, dim3 grid, dim3 block, hipStream_t st, const Step3D
         return false;                                                                \
     } while (0)
     switch (var) {
-    case 0: K3_TILED((k_step3d<8, 1, 4, NC>), 8);
-    case 1: K3_TILED((k_step3d<8, 2, 4, NC>), 8);
-    case 2: K3_TILED((k_step3d<4, 2, 4, NC>), 4);
-    case 3: K3_TILED((k_step3d<4, 2, 3, NC>), 4);
-    case 4: K3_TILED((k_step3d<16, 1, 2, NC>), 16);
-    case 5: K3_TILED((k_step3d<16, 2, 2, NC>), 16);
     case 6: K3_TILED((k_step3d_aligned<8, 4, 1, NC>), 8);
     case 7: K3_TILED((k_step3d_aligned<16, 2, 1, NC>), 16);
     case 8: K3_TILED((k_step3d_aligned<4, 5, 1, NC>), 4);
     case 12: K3_TILED((k_step3d_aligned<8, 2, 2, NC>), 8);
     case 13: K3_TILED((k_step3d_aligned<8, 3, 2, NC>), 8);
     case 14: K3_TILED((k_step3d_aligned<16, 1, 2, NC>), 16);
-    case 9: hipLaunchKernelGGL((k_step3d_direct<4, NC>), grid, block, 0, st, A); return true;
-    case 10: hipLaunchKernelGGL((k_step3d_direct<8, NC>), grid, block, 0, st, A); return true;
-    case 11: hipLaunchKernelGGL((k_step3d_direct<16, NC>), grid, block, 0, st, A); return true;
     default: return false;
     }
 #undef K3_TILED
@@ -1495,6 +1335,38 @@ static at_status at3_launch_f2(at_ctx *ctx, const double *uin, double *uout, int
     return AT_OK;
 }
 
+// one step at any block widths (k_step3d_point)
+static at_status at3_launch_point(at_ctx *ctx, const Step3D &A)
+{
+    Point3D G;
+    // strips of rows whose planes are at least eight workgroups, so that the
+    // last, partly filled one of a plane is a small part of it
+    const int64_t rows = (8 * kPointThreads + A.nx - 1) / A.nx;
+    G.rows = (int32_t)(rows < A.ny ? rows : A.ny);
+    G.plane_wgs = (uint32_t)((G.rows * A.nx + kPointThreads - 1) / kPointThreads);
+    const int64_t strips = (A.ny + G.rows - 1) / G.rows;
+    const int64_t total = strips * A.nz * G.plane_wgs;      // < 2^31 points / 256 x 2
+    G.strip_wgs = (uint32_t)(A.nz * G.plane_wgs);
+    G.total = (uint32_t)total;
+    G.per = (uint32_t)((total + 7) / 8);
+    G.dnx = make_div31((uint32_t)A.nx);
+    G.dWx = make_div31((uint32_t)A.Wx);
+    G.dWy = make_div31((uint32_t)A.Wy);
+    const dim3 grid(8 * G.per), block(kPointThreads);
+    hipStream_t st = at_ctx_stream(ctx);
+    switch (A.nc) {
+    case 3: hipLaunchKernelGGL(k_step3d_point<3>, grid, block, 0, st, A, G); break;
+    case 4: hipLaunchKernelGGL(k_step3d_point<4>, grid, block, 0, st, A, G); break;
+    case 5: hipLaunchKernelGGL(k_step3d_point<5>, grid, block, 0, st, A, G); break;
+    case 6: hipLaunchKernelGGL(k_step3d_point<6>, grid, block, 0, st, A, G); break;
+    case 7: hipLaunchKernelGGL(k_step3d_point<7>, grid, block, 0, st, A, G); break;
+    default: return at_fail(AT_ERR_ARG, "no 3D build for this component count");
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return at_fail(AT_ERR_HIP, hipGetErrorString(e));
+    return AT_OK;
+}
+
 at_status at3_launch(at_ctx *ctx, const double *uin, double *uout, int64_t n0, int s, int publish)
 {
     if (s == 2) return at3_launch_f2(ctx, uin, uout, n0);
@@ -1502,10 +1374,11 @@ at_status at3_launch(at_ctx *ctx, const double *uin, double *uout, int64_t n0, i
     Step3D A;
     fill_step3d(ctx, uin, uout, n0, publish, A);
     const int var = at3_single_variant(at_ctx_cfg(ctx), at_ctx_variant(ctx));
+    if (!at3_is_aligned(var)) return at3_launch_point(ctx, A);
     const int TYv = k3_rows(var);
-    const int64_t gx = (A.nx + TX - 1) / TX, gy = (A.ny + TYv - 1) / TYv;
+    const int64_t gx = A.nx / TX, gy = A.ny / TYv;
     A.ZC = zchunk(A.nz, gx * gy);
-    if (is_aligned(var) && A.ZC > (kZB - 2) * A.Wz) A.ZC = (kZB - 2) * A.Wz;   // LDS delay table
+    if (A.ZC > (kZB - 2) * A.Wz) A.ZC = (kZB - 2) * A.Wz;   // LDS delay table
     const int64_t gz = (A.nz + A.ZC - 1) / A.ZC;
     const dim3 grid((unsigned)gx, (unsigned)gy, (unsigned)gz), block(TX, TYv);
     hipStream_t st = at_ctx_stream(ctx);
