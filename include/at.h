@@ -225,9 +225,9 @@ at_status at_autotune(at_ctx *ctx, const double *u0, double *t1, double *t2,
                       int32_t trial_steps, int32_t *chosen);
 
 /* Kernel variant of a 3D context (results are bit-identical for every
- * variant; at_autotune picks one for 3D contexts): 0..5 and 9..11
- * any block widths (one kernel; 0..5 keep an upper bound on the scalars),
- * 6..8 and 12..14 LDS-tiled with halos in the tile rims and 1 to 4 planes
+ * variant; at_autotune picks one for 3D contexts): any block
+ * widths: 1..5 by bricks, 9..11 one thread per point, 0 one of the two by
+ * size; 6..8 and 12..14 LDS-tiled with halos in the tile rims and 1 to 4 planes
  * prefetched (block widths multiples of the tile, AT_ERR_ARG otherwise), 15
  * and 16 two steps per launch (levels n ->
  * n+2 in one z-march of 64 x 8 or 64 x 4 tiles: each workgroup recomputes

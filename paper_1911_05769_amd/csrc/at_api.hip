@@ -200,6 +200,7 @@ struct at_ctx {
     int64_t n;
     int fuse;
     int variant;     // 3D kernel variant (tile rows, prefetch depth, register budget)
+    int32_t brick[4] = {0, 0, 0, 0};   // 3D: brick of the general kernel (0: not picked yet)
     int kind = 0;    // 1D: region kind of the fused launches (fused_shape), 0 automatic
     int adj_fuse = 0;   // reverse steps per adjoint launch: 0 automatic, 1 one-step kernel
     int debug = 0;      // AT_DEBUG_* flags (at_set_debug)
@@ -508,6 +509,7 @@ void at_ctx_coefs(const at_ctx *c, double *c1, double *c2)
 }
 at_status at_fail(at_status st, const char *msg) { return fail(st, "%s", msg); }
 int at_ctx_variant(const at_ctx *c) { return c->variant; }
+int32_t (*at_ctx_brick(at_ctx *c))[4] { return &c->brick; }
 }
 
 namespace {
@@ -1057,8 +1059,8 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
         if (whole_ppt(c) != 0) cands.push_back({-kWholeVariant, 0});   // one launch per run
     } else {
         for (int v = 0; v < at3_variants(); ++v)
-            if (at3_variant_ok(&c->cfg, v) && (at3_is_aligned(v) || at3_is_fused(v) || cands.empty()))
-                cands.push_back({v, at3_is_fused(v) ? 2 : 1});   // (the others are one kernel)
+            if (at3_variant_ok(&c->cfg, v) && (at3_is_aligned(v) || at3_is_fused(v) || cands.empty() || v == 9))
+                cands.push_back({v, at3_is_fused(v) ? 2 : 1});   // (the others are one of two kernels)
     }
     hipEvent_t e0, e1;
     AT_HIP(hipEventCreate(&e0));

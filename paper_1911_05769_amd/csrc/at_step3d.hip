@@ -23,7 +23,10 @@
 // Work decomposition: blocks that are multiples of a 64 x 8 x-y tile march it
 // through z (k_step3d_aligned, 2.5D: the planes z-1 .. z+2 in registers, the
 // current plane with one-point rims in a double-buffered LDS tile); any other
-// block widths run one thread per point (k_step3d_point).
+// block widths run bricks of a block from LDS (k_step3d_brick) or one thread per
+// point (k_step3d_point).
+#include <algorithm>
+
 #include "../../include/at.h"
 #include "at_internal.h"
 #include "at_ws.h"
@@ -37,6 +40,7 @@ int at_ctx_R(const at_ctx *c);
 hipStream_t at_ctx_stream(const at_ctx *c);
 void at_ctx_coefs(const at_ctx *c, double *c1, double *c2);
 int at_ctx_variant(const at_ctx *c);
+int32_t (*at_ctx_brick(at_ctx *c))[4];
 
 namespace atk {
 
@@ -90,6 +94,7 @@ __device__ __forceinline__ unsigned div31(unsigned n, Div31 d) { return __umulhi
 
 Div31 make_div31(uint32_t d)
 {
+    if (d < 2) return Div31{0, 0};    // (the callers do not divide by 1)
     uint32_t s = 1;
     while (((uint64_t)1 << s) < d) ++s;
     const unsigned __int128 num = (unsigned __int128)1 << (31 + s);
@@ -105,6 +110,20 @@ struct Point3D {
 };
 
 constexpr int kPointThreads = 256;
+
+// The bricks of k_step3d_brick: ex x ey x ez points (the last of a block along
+// an axis may be smaller), nbx x nby x nbz of them to a block, ex * ey * kz
+// threads
+struct Brick3D {
+    uint32_t total, per;      // bricks; an XCD's share of them
+    int32_t ex, ey, ez, kz, nbx, nby, nbz;
+    Div31 dex, dey;           // by ex and ey, and by the last brick's
+    Div31 dex1, dey1;
+};
+
+constexpr int kBrickThreads = 640;    // at most
+constexpr int kBrickPts = 4;      // points and rim elements of a thread, at most
+constexpr int kBrickRims = 3;
 
 // Any block widths: one thread per point, every neighbour straight from the
 // field (L1/L2 serve the re-reads), the AT halo values of the up to three faces
@@ -234,6 +253,180 @@ __global__ __launch_bounds__(kPointThreads) void k_step3d_point(Step3D A, Point3
             if (xl || xh) base[(xl ? A.foff[0] : A.foff[1]) + c * A.psz[0] + px] = ov[c];
             if (yl || yh) base[(yl ? A.foff[2] : A.foff[3]) + c * A.psz[1] + py] = ov[c];
             if (zl || zh) base[(zl ? A.foff[4] : A.foff[5]) + c * A.psz[2] + pz] = ov[c];
+        }
+    }
+}
+
+// Any block widths, by bricks: a workgroup steps one brick of ex x ey x ez
+// points of a block from LDS.  ex * ey * kz threads; thread (cx, cy, cz) owns
+// the points (cx, cy, cz + i kz), so no index is divided per point.  The brick
+// comes in with two trips to memory: the points and (lanes 0 to 5) the face
+// delays, then the rim, one element per lane whichever face it lies on: across
+// a block face the AT value of the facing face's ring levels n-k, n-k-1
+// (section 2, Eq. (1); with k = 0 level n, which the step before published, or
+// the run's start), contiguous along the face; inside a block the field.  What
+// bounds k_step3d_point on small blocks, a lane's own trips and address
+// arithmetic for every neighbour of every point, is done here once per rim
+// element.  120^3 points in blocks of 12^3 (us per step): 50 by points, 33
+// by bricks (145 MB of field and ring per step, 4.3 TB/s).
+template <int NC>
+__global__ __launch_bounds__(kBrickThreads) void k_step3d_brick(Step3D A, Brick3D G)
+{
+    extern __shared__ double tile[];                  // [NC][ez + 2][ey + 2][ex + 2]
+    __shared__ const double *fp0[6], *fp1[6];         // levels n-k and n-k-1 of the facing faces
+    __shared__ int fk[6];                             // their delays; -1: a rim inside the block
+    const int tid = threadIdx.x;
+    const int ny = (int)A.ny;
+    const int64_t plane = A.nx * A.ny;
+    // ---- this workgroup's block and brick (uniform)
+    const unsigned bricks = (unsigned)(G.nbx * G.nby * G.nbz);
+    const unsigned wid = blockIdx.x / 8 + (blockIdx.x % 8) * G.per;
+    if (wid >= G.total) return;
+    const unsigned blk = wid / bricks, br = wid - blk * bricks;
+    const int bx = (int)(blk % (unsigned)A.Px), by = (int)(blk / (unsigned)A.Px % (unsigned)A.Py);
+    const int bz = (int)(blk / ((unsigned)A.Px * (unsigned)A.Py));
+    const int lx0 = (int)(br % (unsigned)G.nbx) * G.ex, ly0 = (int)(br / (unsigned)G.nbx % (unsigned)G.nby) * G.ey;
+    const int lz0 = (int)(br / (unsigned)(G.nbx * G.nby)) * G.ez;
+    const int ex = min(G.ex, A.Wx - lx0), ey = min(G.ey, A.Wy - ly0), ez = min(G.ez, A.Wz - lz0);
+    const int SX = G.ex + 2, SXY = SX * (G.ey + 2), SC = SXY * (G.ez + 2);
+    const double *U0 = A.uin + ((int64_t)(bz * A.Wz + lz0) * ny + by * A.Wy + ly0) * A.nx +
+                       bx * A.Wx + lx0;               // the brick's first point
+    const int64_t first = U0 - A.uin;
+    // ---- trip 1: the face delays (lanes 0 to 5; -1: no face of the block), then
+    // the points, which stay in flight while the rim's addresses are formed
+    int k = -1;
+    if (tid < 6) {
+        const int a = tid >> 1, hi = tid & 1;
+        const int at0 = a == 0 ? lx0 : (a == 1 ? ly0 : lz0), ext = a == 0 ? ex : (a == 1 ? ey : ez);
+        const int W = a == 0 ? A.Wx : (a == 1 ? A.Wy : A.Wz);
+        if (hi ? at0 + ext == W : at0 == 0) k = A.delays[A.n * A.F + 6 * (int64_t)blk + tid];
+    }
+    const int cq = (int)div31((unsigned)tid, G.dex);
+    const int cx = tid - cq * G.ex, cz = (int)div31((unsigned)cq, G.dey);
+    const int cy = cq - cz * G.ey;
+    const bool col = cx < ex && cy < ey;
+    const int fcol = cy * (int)A.nx + cx;
+    double u[kBrickPts][NC];
+#pragma unroll
+    for (int i = 0; i < kBrickPts; ++i) {
+        const int z = cz + i * G.kz;
+        if (col && z < ez) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) u[i][c] = U0[c * A.npt + z * plane + fcol];
+        }
+    }
+    // ---- the faces' ring levels
+    if (tid < 6) {
+        const int a = tid >> 1;
+        if (k >= 0) {
+            const int d = tid & 1 ? 1 : -1;
+            const int n0 = a == 0 ? wrap32(bx + d, A.Px) : bx, n1 = a == 1 ? wrap32(by + d, A.Py) : by;
+            const int n2 = a == 2 ? wrap32(bz + d, A.Pz) : bz;
+            const int64_t off = (((int64_t)n2 * A.Py + n1) * A.Px + n0) * A.bstride + A.foff[tid ^ 1];
+            int s0 = A.slot0 - k;
+            if (s0 < 0) s0 += A.R;
+            int s1 = s0 - 1;
+            if (s1 < 0) s1 += A.R;
+            fp0[tid] = A.ring + s0 * A.level + off;
+            fp1[tid] = k > 0 && !A.stale ? A.ring + s1 * A.level + off : fp0[tid];
+        }
+        fk[tid] = k;
+    }
+    __syncthreads();
+    // ---- trip 2: the rim, element r of the faces x-, x+, y-, y+, z-, z+ in turn
+    const int nxf = ey * ez, nyf = ex * ez, nzf = ex * ey;
+    const int nrim = 2 * (nxf + nyf + nzf);
+    double v0[kBrickRims][NC], v1[kBrickRims][NC];
+    int rk[kBrickRims], rat[kBrickRims];
+#pragma unroll
+    for (int i = 0; i < kBrickRims; ++i) {
+        int r = tid + i * (int)blockDim.x;
+        rat[i] = -1;
+        rk[i] = 0;
+        if (r < nrim) {
+            int a = 0, nf = nxf;
+            if (r >= 2 * nxf) { r -= 2 * nxf; a = 1; nf = nyf; }
+            if (a == 1 && r >= 2 * nyf) { r -= 2 * nyf; a = 2; nf = nzf; }
+            const int hi = r >= nf ? 1 : 0;
+            r -= hi * nf;
+            // (q, p): slow and fast coordinate in the face
+            const int wf = a == 0 ? ey : ex;
+            const Div31 dw = a == 0 ? (ey == G.ey ? G.dey : G.dey1) : (ex == G.ex ? G.dex : G.dex1);
+            const int q = wf == 1 ? r : (int)div31((unsigned)r, dw);
+            const int p = r - q * wf;
+            const int x = a == 0 ? (hi ? ex : -1) : p;
+            const int y = a == 0 ? p : (a == 1 ? (hi ? ey : -1) : q);
+            const int z = a == 2 ? (hi ? ez : -1) : q;
+            rat[i] = (z + 1) * SXY + (y + 1) * SX + x + 1;
+            const int f = 2 * a + hi;
+            rk[i] = fk[f];
+            if (rk[i] >= 0) {
+                const int pos = a == 0 ? (lz0 + q) * A.Wy + ly0 + p
+                                       : (a == 1 ? (lz0 + q) * A.Wx + lx0 + p : (ly0 + q) * A.Wx + lx0 + p);
+                const double *p0 = fp0[f] + pos, *p1 = fp1[f] + pos;
+                const int64_t ps = A.psz[0] * (a == 0) + A.psz[1] * (a == 1) + A.psz[2] * (a == 2);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) { v0[i][c] = p0[c * ps]; v1[i][c] = p1[c * ps]; }
+            } else {
+                const double *p0 = A.uin + (first + z * plane + (int64_t)y * A.nx + x);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) v0[i][c] = v1[i][c] = p0[c * A.npt];
+            }
+        }
+    }
+    const int tcol = (cy + 1) * SX + cx + 1;
+#pragma unroll
+    for (int i = 0; i < kBrickPts; ++i) {
+        const int z = cz + i * G.kz;
+        if (col && z < ez) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) tile[c * SC + (z + 1) * SXY + tcol] = u[i][c];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kBrickRims; ++i) {
+        if (rat[i] >= 0) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+                tile[c * SC + rat[i]] = at_h(rk[i], A.stale != 0, v0[i][c], v1[i][c]);
+        }
+    }
+    __syncthreads();
+    // ---- the step, and the level-(n+1) values of block faces to the ring
+    const int64_t slot = A.slot0 + 1 == A.R ? 0 : A.slot0 + 1;
+    double *base = A.ring + slot * A.level + (int64_t)blk * A.bstride;
+    const int lx = lx0 + cx, ly = ly0 + cy;
+#pragma unroll
+    for (int i = 0; i < kBrickPts; ++i) {
+        const int z = cz + i * G.kz;
+        if (!(col && z < ez)) continue;
+        const double *t0 = tile + (z + 1) * SXY + tcol;
+        double *out = A.uout + first + z * plane + fcol;
+        double ov[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const double *t = t0 + c * SC;
+            const double w = u[i][c];
+            const double xl = t[-1], xh = t[1], yl = t[-SX], yh = t[SX], zl = t[-SXY], zh = t[SXY];
+            const double D1x = (xh - xl) * A.c1[0], D2x = ((xh - 2.0 * w) + xl) * A.c2[0];
+            const double D1y = (yh - yl) * A.c1[1], D2y = ((yh - 2.0 * w) + yl) * A.c2[1];
+            const double D1z = (zh - zl) * A.c1[2], D2z = ((zh - 2.0 * w) + zl) * A.c2[2];
+            const double lap = (D2x + D2y) + D2z;
+            const double adv = (u[i][0] * D1x + u[i][1] * D1y) + u[i][2] * D1z;
+            ov[c] = w + A.dt * (A.kappa[c] * lap - adv);
+            out[c * A.npt] = ov[c];
+        }
+        const int lz = lz0 + z;
+        const bool fx = lx == 0 || lx == A.Wx - 1, fy = ly == 0 || ly == A.Wy - 1;
+        const bool fz = lz == 0 || lz == A.Wz - 1;
+        if (A.publish && (fx || fy || fz)) {
+            const int px = lz * A.Wy + ly, py = lz * A.Wx + lx, pz = ly * A.Wx + lx;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                if (fx) base[(lx == 0 ? A.foff[0] : A.foff[1]) + c * A.psz[0] + px] = ov[c];
+                if (fy) base[(ly == 0 ? A.foff[2] : A.foff[3]) + c * A.psz[1] + py] = ov[c];
+                if (fz) base[(lz == 0 ? A.foff[4] : A.foff[5]) + c * A.psz[2] + pz] = ov[c];
+            }
         }
     }
 }
@@ -1085,9 +1278,9 @@ uint64_t at3_ring_level_doubles(const at_config *c)
 }
 
 // kernel variants the autotuner may choose from (tile rows, prefetch depth,
-// register budget); every variant performs the same operations.  0 to 5 and 9
-// to 11 are k_step3d_point, 6 to 8 and 12 to 14 k_step3d_aligned.  Variants
-// 15 and 16 advance two steps per launch (k_step3d_f2 with 8 and 4 tile rows).
+// register budget); every variant performs the same operations.  1 to 5 are
+// k_step3d_brick, 9 to 11 k_step3d_point, 0 one of the two by size, 6 to 8 and
+// 12 to 14 k_step3d_aligned.  Variants 15 and 16 advance two steps per launch (k_step3d_f2 with 8 and 4 tile rows).
 int at3_variants() { return 17; }
 static int k3_rows(int var)
 {
@@ -1367,6 +1560,86 @@ static at_status at3_launch_point(at_ctx *ctx, const Step3D &A)
     return AT_OK;
 }
 
+// The brick for blocks of Wx x Wy x Wz points at nc components: of the even
+// splits of each axis whose tile fits kBrickLds and whose points and rims fit
+// the threads, the one with the least work per block, counted as its threads'
+// slots (4 a point, 2 a rim element: a point is loaded, stepped and stored)
+// plus a fixed cost per workgroup, more where a CU holds one workgroup only.
+// Measured (us per step) at tiles of at most 26, 40, 52, 80 and 120 KB: 120^3 in
+// 12^3 blocks 47, 38, 38, 33, 33, with two scalars 72, 89, 76, 77, 60; 300^3 in
+// 50^3 blocks 589, 538, 510, 464, 538; 256^3 in 64^3 with two scalars 481, 494,
+// 467, 420, 579.
+static bool pick_brick(int64_t Wx, int64_t Wy, int64_t Wz, int nc, int32_t (&e)[4])
+{
+    constexpr int64_t kBrickLds = 120 * 1024;
+    double best = 1e300;
+    int64_t ex = 0, ey = 0, ez = 0;
+    for (int64_t nx = 1; nx <= Wx; ++nx) {            // even splits, each width once
+        if ((Wx + nx - 1) / nx == ex || (Wx + nx - 1) / nx > 64) continue;
+        ex = (Wx + nx - 1) / nx;
+        if (ex < 2 || Wx / ex > 64) break;
+        for (int64_t ny = 1; ny <= Wy; ++ny) {
+            if ((Wy + ny - 1) / ny == ey || (Wy + ny - 1) / ny * ex > kBrickThreads) continue;
+            ey = (Wy + ny - 1) / ny;
+            if (ey < 2) break;
+            for (int64_t nz = 1; nz <= Wz; ++nz) {
+                if ((Wz + nz - 1) / nz == ez || (Wz + nz - 1) / nz > 64) continue;
+                ez = (Wz + nz - 1) / nz;
+                const int64_t lds = (ex + 2) * (ey + 2) * (ez + 2) * nc * 8;
+                if (lds > kBrickLds) continue;
+                const double alone = lds > 80 * 1024 ? 1.25 : 1.0;     // one workgroup per CU
+                const int64_t rims = 2 * (ex * ey + ey * ez + ex * ez);
+                const double count = (double)((Wx + ex - 1) / ex * ((Wy + ey - 1) / ey) * ((Wz + ez - 1) / ez));
+                for (int64_t kz = 1; kz <= ez && ex * ey * kz <= kBrickThreads; ++kz) {
+                    const int64_t nt = ex * ey * kz, nt64 = (nt + 63) / 64 * 64;
+                    const int64_t pts = (ez + kz - 1) / kz, rm = (rims + nt - 1) / nt;
+                    if (pts > kBrickPts || rm > kBrickRims) continue;
+                    const double cost = alone * count * ((double)nt64 * (4 * pts + 2 * rm) + 1500.0);
+                    if (cost < best) {
+                        best = cost;
+                        e[0] = (int32_t)ex; e[1] = (int32_t)ey; e[2] = (int32_t)ez; e[3] = (int32_t)kz;
+                    }
+                }
+            }
+            ez = 0;
+        }
+        ey = 0;
+    }
+    return best < 1e300;
+}
+
+// one step by bricks; false: no brick for this block shape and component count
+static bool at3_launch_brick(at_ctx *ctx, const Step3D &A)
+{
+    int32_t (&e)[4] = *at_ctx_brick(ctx);             // picked once per context
+    if (e[0] == 0 && !pick_brick(A.Wx, A.Wy, A.Wz, A.nc, e)) e[0] = -1;
+    if (e[0] < 0) return false;
+    Brick3D G;
+    G.ex = e[0]; G.ey = e[1]; G.ez = e[2]; G.kz = e[3];
+    G.nbx = (A.Wx + G.ex - 1) / G.ex;
+    G.nby = (A.Wy + G.ey - 1) / G.ey;
+    G.nbz = (A.Wz + G.ez - 1) / G.ez;
+    const int64_t total = (int64_t)A.Px * A.Py * A.Pz * G.nbx * G.nby * G.nbz;
+    if (total >= (int64_t)1 << 31) return false;
+    G.total = (uint32_t)total;
+    G.per = (uint32_t)((total + 7) / 8);
+    G.dex = make_div31((uint32_t)G.ex);
+    G.dey = make_div31((uint32_t)G.ey);
+    G.dex1 = make_div31((uint32_t)(A.Wx - (G.nbx - 1) * G.ex));
+    G.dey1 = make_div31((uint32_t)(A.Wy - (G.nby - 1) * G.ey));
+    const dim3 grid(8 * G.per), block((unsigned)(G.ex * G.ey * G.kz));
+    const size_t lds = (size_t)(G.ex + 2) * (G.ey + 2) * (G.ez + 2) * A.nc * 8;
+    hipStream_t st = at_ctx_stream(ctx);
+    switch (A.nc) {
+    case 3: hipLaunchKernelGGL(k_step3d_brick<3>, grid, block, lds, st, A, G); return true;
+    case 4: hipLaunchKernelGGL(k_step3d_brick<4>, grid, block, lds, st, A, G); return true;
+    case 5: hipLaunchKernelGGL(k_step3d_brick<5>, grid, block, lds, st, A, G); return true;
+    case 6: hipLaunchKernelGGL(k_step3d_brick<6>, grid, block, lds, st, A, G); return true;
+    case 7: hipLaunchKernelGGL(k_step3d_brick<7>, grid, block, lds, st, A, G); return true;
+    default: return false;
+    }
+}
+
 at_status at3_launch(at_ctx *ctx, const double *uin, double *uout, int64_t n0, int s, int publish)
 {
     if (s == 2) return at3_launch_f2(ctx, uin, uout, n0);
@@ -1374,7 +1647,19 @@ at_status at3_launch(at_ctx *ctx, const double *uin, double *uout, int64_t n0, i
     Step3D A;
     fill_step3d(ctx, uin, uout, n0, publish, A);
     const int var = at3_single_variant(at_ctx_cfg(ctx), at_ctx_variant(ctx));
-    if (!at3_is_aligned(var)) return at3_launch_point(ctx, A);
+    if (!at3_is_aligned(var)) {
+        // variant 0: bricks, but points on grids of a few waves per CU, where a brick's
+        // three phases cost more than its loads save, and for blocks of less
+        // than half a wave (us per step by points and by bricks: 17 x 19 x 23:
+        // 5.2 and 9.0; 400 x 400 x 4: 15.5 both; 64 x 300 x 200: 62 and 48; 64^3
+        // in 2^3 blocks: 20 and 52; 128^3 in 4^3 blocks: 108 and 78)
+        const bool points = var >= 9 || (var == 0 && (A.npt <= 65536 ||
+                                                      (int64_t)A.Wx * A.Wy * A.Wz < 32));
+        if (points || !at3_launch_brick(ctx, A)) return at3_launch_point(ctx, A);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return at_fail(AT_ERR_HIP, hipGetErrorString(e));
+        return AT_OK;
+    }
     const int TYv = k3_rows(var);
     const int64_t gx = A.nx / TX, gy = A.ny / TYv;
     A.ZC = zchunk(A.nz, gx * gy);
