@@ -1001,11 +1001,9 @@ at_status at_run_ws(at_ctx *c, double *u, double *scratch, int64_t nsteps, int32
                     (long long)d.P, (long long)maxt);
     if (nsteps == 0) return AT_OK;
     int32_t *err = c->sync + 2 * d.P;
-    AT_HIP(launch_ws_init(c->sync, 2 * d.P, -1, err, c->st));
     Ws1D a{};
     a.u = u;
     a.ring = c->ring;
-    a.cnt = c->sync;
     a.err = err;
     a.delays = c->delays;
     a.P = d.P;

@@ -75,7 +75,6 @@ struct AdjF {
 struct Ws1D {
     double *u;                // field, advanced in place: double[N]
     double *ring;             // edge levels: [R][P][2][h], level n in slot n mod R
-    int32_t *cnt;             // newest announced level per tile edge: [P][2] (-1: none)
     int32_t *err;             // 0, or 1 once a wait passed the spin limit
     int8_t *delays;           // delays used, recorded: k[n][2P]
     int64_t P, W, n0, nsteps;

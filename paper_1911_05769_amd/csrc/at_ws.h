@@ -1,6 +1,6 @@
-// Helpers of the weakly-synchronous runs of libat.so (1D and 3D): bounded
-// polling of per-edge / per-block level counters, the announce after
-// device-coherent ring stores, and the idle-time noise.
+// Helpers of the weakly-synchronous runs of libat.so (1D and 3D): device-coherent
+// loads and stores, bounded polling of the 3D run's per-block level counters,
+// and the idle-time noise.
 #pragma once
 
 #include "at_internal.h"
@@ -50,15 +50,6 @@ __device__ __forceinline__ void st_coherent(double *p, double v)
 __device__ __forceinline__ int32_t load_relaxed(const int32_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Announce level v on a counter: the device-coherent ring stores issued
-// before it have completed (vmcnt 0) when the counter store is issued, so a
-// reader that sees v and then loads the ring sees the values.
-__device__ __forceinline__ void announce(int32_t *p, int32_t v)
-{
-    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Wait until the counter announces at least level `need`; returns the newest
