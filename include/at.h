@@ -258,7 +258,7 @@ at_status at_query(const at_ctx *ctx, int64_t *n, int32_t *fuse_steps, int32_t *
 at_status at_delays_copy(const at_ctx *ctx, int8_t *host_out);
 
 /* Snapshot / restore of the full stepper state (the field u at the current
- * step, the ring and n).  at_snapshot_bytes gives the device buffer size.
+ * step, the ring levels later steps read and n).  at_snapshot_bytes gives the device buffer size.
  * Both are asynchronous on the context's stream.  at_restore of a buffer that
  * this context filled by at_snapshot (recognised by its address) takes the
  * step from the context; any other buffer is read once on the host to find
