@@ -1,4 +1,5 @@
-// Discrete adjoint of the 1D AT stepper (reverse mode), one launch per step.
+// Discrete adjoint of the 1D AT stepper (reverse mode): k_adj1d, one launch per
+// step, and k_adj1d_wave, several steps per launch.
 //
 // The forward step at level n is u'_i = u_i + dt*(nu*D2_i - a_i*D1_i) with
 // the central stencils of section 3.2 and, at a tile edge, halo values
@@ -18,7 +19,11 @@
 // j = n' - k[n'] - n of every mu^{n'} of the face it feeds.  mu^n itself is
 // recomputed in place from lambda^{n+1} and u^n, which the workgroup holds.
 // Each workgroup keeps one compensated dJ/dnu accumulator across launches.
+#include <type_traits>
+
 #include "at_internal.h"
+#include "at_stencil1d.h"
+#include "at_wave.h"
 
 namespace atk {
 
@@ -46,17 +51,6 @@ __device__ __forceinline__ Partials<ORDER> partials(double c1, double c2)
         p.g2u = -30.0 * c2;
     }
     return p;
-}
-
-__device__ __forceinline__ double extrap(int kk, bool stale, double v0, double v1, double v2,
-                                         int M)
-{
-    if (stale) return v0;
-    const double dk = (double)kk;
-    const double d1 = v0 - v1;
-    if (M == 2) return v0 + dk * d1;
-    const double w2 = 0.5 * dk * (dk + 1.0);
-    return (v0 + dk * d1) + w2 * (d1 - (v1 - v2));
 }
 
 // dH/dv_j
@@ -174,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void k_adj1d(Adj1D a)
                             vv[j] = a.ring[((lev * a.P + stp) * 2 + (1 - side)) * H + q];
                         }
                     }
-                    v = extrap(kk, stale, vv[0], vv[1], vv[2], M);
+                    v = extrap<false>(kk, stale, vv[0], vv[1], vv[2], M);
                 }
             }
             nb[s] = v;
@@ -258,294 +252,129 @@ __device__ __forceinline__ int64_t fdiv(int64_t a, int64_t b)
 }
 
 
-// S reverse steps in one launch.  The workgroup's region is its owned chunk
-// plus S*h points on each side; every reverse step reads lambda and u within
-// h points (across a tile face: the mu of that face, computed from points
-// within h of it), so after S steps the owned points are exact while the
-// rims have gone stale, as in the forward fused launches.  lambda stays in
-// registers; each step reads its level of u (the recomputed segment), the
-// next level's loads in flight meanwhile.  In LDS: the delay rows of the
-// launch's gather window, the record-mode ring levels that the forward
-// halos of these steps read, and the mu of every face of the region for
-// levels nt-S .. nt-1 (computed here) and nt .. nt+L+m-2 (from the mu ring).
+// a + x with the rounding error of the sum collected as in acc_add, by six
+// additions instead of a comparison and selections
+__device__ __forceinline__ void acc_add_nobranch(Acc &a, double x)
+{
+    const double t = a.s + x;
+    const double y = t - a.s;
+    a.c += (a.s - (t - y)) + (x - y);
+    a.s = t;
+}
+
+// S reverse steps in one launch, one wave per region: RT rim lanes, CT owned
+// lanes, RT rim lanes of PPT points each (RAGGED: the first nf lanes of a tile
+// PPT, the others PPT - 1, so that any tile width has its lanes).  Every reverse step reads lambda and
+// u within h points (across a tile face: the mu of that face, computed from
+// points within h of it), so the rims go stale by h points per step, as in the
+// forward fused launches (at_wave1d.h); lambda and the levels of u stay in
+// registers and neighbours' values move by DPP, so no step has a barrier.
+//   * The levels of u are recomputed here, K at a time: a group's lowest level
+//     comes from the segment store (every K-th level of the segment), the other
+//     K - 1 by forward steps with the recorded delays and edge levels, then the
+//     K reverse steps run on them.  The recomputed levels go stale by at most
+//     (K - 1) h points from the region's ends, hence rims of (S + K) h points.
+//     What bounds this is instruction issue (29 FP64 instructions per
+//     point for the reverse step of order 2, 10 for the recomputed one); with
+//     every level stored and read back, by 256-thread regions with a barrier per
+//     step, a gradient moved 16 bytes per point and step for u alone and the
+//     reverse step waited on its latencies.  2^20 points, order 2, 1000 steps (us
+//     per step): rebuild 1.7 and reverse 3.0 that way, 0.9 and 2.9 this way
+//     (500 tiles of 1003 points, until then one step per launch, reverse: 2.0).
+//   * In LDS: the delay rows of the launch's gather window, the record-mode ring
+//     levels that the halos of these steps read, and the mu of every face of the
+//     region for levels nt .. nt+L+m-2 (from the mu ring), gathered into sums for
+//     the levels computed here; their own mu is added as it is computed.
 // Each point's lambda^n is summed in the same order as the one-step kernel.
-template <int ORDER, bool LINEAR, int PPT>
-__global__ __launch_bounds__(kThreads) void k_adj1d_fused(AdjF a)
+template <int ORDER, bool LINEAR, bool FMA, int PPT, bool RAGGED>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PPT >= 6 ? 2 : 3)))
+void k_adj1d_wave(AdjF a)
 {
     constexpr int H = ORDER / 2;
     constexpr int M = (ORDER == 2) ? 2 : 3;
     constexpr int NS = 2 * H;
+    constexpr int K = kAdjGroup;
     extern __shared__ double lds[];
     const int S = a.S, NT = a.NT;
     const int DW = a.L + M - 1;               // gather window beyond the step, in levels
     const int LV = S + DW;                    // levels held per history table
-    double *xch = lds;                                        // [2][2 arrays][2H][kThreads]
-    double *eh = xch + 2 * 2 * NS * kThreads;                 // [LV][NT][2][H]: u edges, levels nt-S-DW ..
+    double *eh = lds;                                         // [LV][NT][2][H]: u edges, levels nt-S-DW ..
     double *muh = eh + (size_t)LV * NT * 2 * H;               // [LV][NT][2][H]: mu, levels nt-S ..
     double *gt = muh + (size_t)LV * NT * 2 * H;               // [S][NT][2][H]: gathered mu, levels nt-S ..
     int8_t *kd = reinterpret_cast<int8_t *>(gt + (size_t)S * NT * 2 * H);     // [LV][NT][2]: rows nt-S ..
 
-    const int tid = threadIdx.x;
-    const int64_t c0 = (int64_t)blockIdx.x * a.CH;
-    const int owned = (int)((a.N - c0 < a.CH) ? (a.N - c0) : a.CH);
-    const int E = a.RL + owned + S * H;                       // region length
-    const int64_t G0 = c0 - a.RL;                             // multiple of PPT
-    const int rp0 = tid * PPT;
-    const int64_t Gt = G0 + rp0;
-    const int64_t tdiv = fdiv(Gt, a.W);
-    const int o0 = (int)(Gt - tdiv * a.W);                    // multiple of PPT
-    const int tl0 = (int)(tdiv - fdiv(G0, a.W));
-    int64_t tp0 = tdiv % a.P;
-    if (tp0 < 0) tp0 += a.P;
-    const bool in_region = rp0 < E;
-    const bool lo_edge = o0 == 0 && in_region;
-    const bool hi_edge = o0 + PPT == a.W && in_region;
-    const bool owns = rp0 >= a.RL && rp0 < a.RL + owned;
-    int64_t gb = Gt % a.N;                                    // a thread's points never straddle the wrap
-    if (gb < 0) gb += a.N;
-    const Partials<ORDER> pd = partials<ORDER>(a.c1, a.c2);
+    const int lane = threadIdx.x;
+    const int tpt = a.tpt, P = (int)a.P, NTH = P * tpt;       // threads of a tile, of the grid
+    const int c0 = blockIdx.x * a.CT;
+    const int owned = NTH - c0 < a.CT ? NTH - c0 : a.CT;
+    const int gA = c0 - a.RT;                                 // unwrapped
+    const int E = a.RT + owned + a.RT;                        // lanes in use
+    int tA = gA / tpt;                                        // tile of lane 0 (unwrapped, floor)
+    if (gA < tA * tpt) --tA;
+    const int iA = gA - tA * tpt;                             // its index in that tile
+    const int tl0 = (iA + lane) / tpt;                        // region-local tile
+    const int ti = iA + lane - tl0 * tpt;
+    int tb = tA % P;
+    if (tb < 0) tb += P;
+    const int tp0 = (tb + tl0) % P;
+    const bool in_region = lane < E;
+    const bool shrt = RAGGED && ti >= a.nf;                   // PPT - 1 points
+    const bool lo_edge = ti == 0 && in_region;
+    const bool hi_edge = ti == tpt - 1 && in_region;          // (RAGGED: always a short one)
+    const bool owns = lane >= a.RT && lane < a.RT + owned;
+    const int64_t gb = (int64_t)tp0 * a.W + ti * PPT - (RAGGED && ti > a.nf ? ti - a.nf : 0);
+    constexpr int LAST = PPT - (RAGGED ? 1 : 0);              // points of a lane with a right face
+    // a lane's points of a field; a short lane's last place holds 0 until its
+    // right neighbour's point takes it
+    auto load = [&](const double *src, double (&to)[PPT]) {
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) to[j] = !RAGGED || j < PPT - 1 || !shrt ? src[gb + j] : 0.0;
+    };
+    const Partials<ORDER> pd = partials<ORDER>(a.coef.c1, a.coef.c2);
     const bool stale = a.stale != 0;
     const int64_t F = 2 * a.P;
     const int64_t nlo = a.nt - S;                             // lowest level computed here
+    const double dt = a.coef.dt, nu = a.coef.nu;
 
-    // ---- LDS tables
+    // ---- lambda^{nt} of the lane's points; LDS tables
+    double lam[PPT];
+    load(a.lam_in, lam);
     {
-        int64_t tb = fdiv(G0, a.W) % a.P;
-        if (tb < 0) tb += a.P;
         const int nk = LV * NT * 2;
-        for (int e = tid; e < nk; e += kThreads) {
+#pragma unroll 4
+        for (int e = lane; e < nk; e += 64) {
             const int side = e & 1;
             const int tl = (e >> 1) % NT;
             const int r = (e >> 1) / NT;
             const int64_t n2 = nlo + r;
-            const int64_t tp = (tb + tl) % a.P;
+            const int tp = (tb + tl) % P;
             kd[e] = n2 < a.nsteps_total ? a.delays[n2 * F + 2 * tp + side] : (int8_t)0;
         }
         const int nh = LV * NT * 2 * H;
-        for (int e = tid; e < nh; e += kThreads) {
+#pragma unroll 2
+        for (int e = lane; e < nh; e += 64) {
             const int q = e % H;
             const int side = (e / H) & 1;
             const int tl = (e / (2 * H)) % NT;
             const int r = (e / (2 * H)) / NT;
-            const int64_t tp = (tb + tl) % a.P;
+            const int tp = (tb + tl) % P;
             const int64_t lev = nlo - DW + r;                 // u edge level
-            if (lev >= 0)
-                eh[e] = a.ring[((lev * a.P + tp) * 2 + side) * H + q];
+            double x = 0.0, y = 0.0;
+            if (lev >= 0) x = a.ring[((lev * a.P + tp) * 2 + side) * H + q];
             const int64_t n2 = nlo + r;                       // mu level
-            if (n2 >= a.nt && n2 < a.nsteps_total) {
-                const int64_t ms = n2 % a.Rmu;
-                muh[e] = a.mu[((ms * a.P + tp) * 2 + side) * H + q];
-            }
+            if (n2 >= a.nt && n2 < a.nsteps_total)
+                y = a.mu[((n2 % a.Rmu * a.P + tp) * 2 + side) * H + q];
+            eh[e] = x;
+            muh[e] = y;
         }
     }
-
-    // ---- lambda^{nt} of the thread's points
-    double lam[PPT];
-#pragma unroll
-    for (int j = 0; j < PPT; ++j) lam[j] = in_region ? a.lam_in[gb + j] : 0.0;
-
-    // P_s(u) = dt*(nu*g2[s] - a*g1[s]) for a compile-time slot s
-    auto Ps = [&](int s, double u) -> double {
-        const double adv = LINEAR ? a.cadv : u;
-        return a.dt * (a.nu * pd.g2[s] - adv * pd.g1[s]);
-    };
-
-    Acc gacc{0.0, 0.0};
-    // one reverse step: level n = nt-1-t from lambda^{n+1} (lam) and u^n (uc);
-    // the loads of u^{n-1} go to un
-    auto rstep = [&](int t, double (&uc)[PPT], double (&un)[PPT]) {
-        const int64_t n = a.nt - 1 - t;
-        {   // unconditional (a level inside the segment), so that the wait for uc
-            // below leaves these loads in flight
-            const int64_t nn = t + 1 < S ? n - 1 : n;
-            const double *src = a.seg + (nn - a.seg_n0) * a.N + gb;
-#pragma unroll
-            for (int j = 0; j < PPT; ++j) un[j] = src[j];
-        }
-        // ---- exchange lambda^{n+1} and u^n edges with the neighbouring threads
-        double *buf = xch + (t & 1) * 2 * NS * kThreads;
-#pragma unroll
-        for (int q = 0; q < H; ++q) {
-            buf[(0 * NS + q) * kThreads + tid] = lam[q];
-            buf[(0 * NS + H + q) * kThreads + tid] = lam[PPT - H + q];
-            buf[(1 * NS + q) * kThreads + tid] = uc[q];
-            buf[(1 * NS + H + q) * kThreads + tid] = uc[PPT - H + q];
-        }
-        __syncthreads();
-        double llo[H], lhi[H], ulo[H], uhi[H];   // raw neighbours: points -H..-1 and PPT..PPT+H-1
-#pragma unroll
-        for (int q = 0; q < H; ++q) {
-            llo[q] = tid > 0 ? buf[(0 * NS + H + q) * kThreads + tid - 1] : 0.0;
-            ulo[q] = tid > 0 ? buf[(1 * NS + H + q) * kThreads + tid - 1] : 0.0;
-            lhi[q] = tid < kThreads - 1 ? buf[(0 * NS + q) * kThreads + tid + 1] : 0.0;
-            uhi[q] = tid < kThreads - 1 ? buf[(1 * NS + q) * kThreads + tid + 1] : 0.0;
-        }
-        // ---- the LDS values of this step's edge work, all loaded before the
-        // first is used so that their latencies overlap: the delays of this
-        // tile's faces, and the delays and gathered sums at level n of the
-        // neighbours' faces that this thread's edge points feed
-        const int krow = (int)(n - nlo);
-        const bool lo_src = lo_edge && tid > 0;   // region ends: no source tile in the tables
-        const bool hi_src = hi_edge && tid < kThreads - 1;
-        int kown[2] = {0, 0}, knb[2] = {1, 1};
-        double gth[2][H];
-#pragma unroll
-        for (int q = 0; q < H; ++q) { gth[0][q] = 0.0; gth[1][q] = 0.0; }
-        if (lo_edge) kown[0] = kd[(krow * NT + tl0) * 2 + 0];
-        if (hi_edge) kown[1] = kd[(krow * NT + tl0) * 2 + 1];
-        if (hi_src) {                             // feeds the next tile's low face
-            knb[0] = kd[(krow * NT + tl0 + 1) * 2 + 0];
-#pragma unroll
-            for (int q = 0; q < H; ++q) gth[0][q] = gt[((krow * NT + tl0 + 1) * 2 + 0) * H + q];
-        }
-        if (lo_src) {                             // feeds the previous tile's high face
-            knb[1] = kd[(krow * NT + tl0 - 1) * 2 + 1];
-#pragma unroll
-            for (int q = 0; q < H; ++q) gth[1][q] = gt[((krow * NT + tl0 - 1) * 2 + 1) * H + q];
-        }
-        // ---- u window with the forward AT halo across the tile faces
-        double uw[PPT + 2 * H];
-#pragma unroll
-        for (int q = 0; q < H; ++q) { uw[q] = ulo[q]; uw[PPT + H + q] = uhi[q]; }
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) uw[H + j] = uc[j];
-        if (lo_edge || hi_edge) {
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                if (side == 0 ? !lo_src : !hi_src) continue;
-                const int kk = kown[side];
-                if (kk > 0) {
-                    const int stl = side == 0 ? tl0 - 1 : tl0 + 1;
-#pragma unroll
-                    for (int q = 0; q < H; ++q) {
-                        double vv[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-                        for (int jj = 0; jj < M; ++jj) {
-                            if (jj == 0 || !stale) {
-                                const int64_t lev = n - kk - jj;
-                                vv[jj] = eh[((((int)(lev - (nlo - DW))) * NT + stl) * 2 + (1 - side)) * H + q];
-                            }
-                        }
-                        const double hv = extrap(kk, stale, vv[0], vv[1], vv[2], M);
-                        if (side == 0) uw[q] = hv;
-                        else uw[PPT + H + q] = hv;
-                    }
-                }
-            }
-        }
-        // lambda and raw u at window index i (-H .. PPT+H-1), compile-time i
-        auto lat = [&](int i) -> double { return i < 0 ? llo[H + i] : (i >= PPT ? lhi[i - PPT] : lam[i]); };
-        auto uat = [&](int i) -> double { return i < 0 ? ulo[H + i] : (i >= PPT ? uhi[i - PPT] : uc[i]); };
-        // mu^n of this step for the face a point feeds, from the raw window
-        auto mu_lo = [&](int q) -> double {         // face of the next tile, low side: its first h points
-            double m = 0.0;
-#pragma unroll
-            for (int e = 0; e < H; ++e)
-                if (e <= q) m += lat(PPT + e) * Ps(q - e, uat(PPT + e));
-            return m;
-        };
-        auto mu_hi = [&](int q) -> double {         // face of the previous tile, high side: its last h points
-            double m = 0.0;
-#pragma unroll
-            for (int e = 0; e < H; ++e)
-                if (e <= H - 1 - q) m += lat(-1 - e) * Ps(H + q + e, uat(-1 - e));
-            return m;
-        };
-        double res[PPT];
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) {
-            const double u = uc[j];
-            double nb[NS];
-#pragma unroll
-            for (int q = 0; q < H; ++q) { nb[q] = uw[j + q]; nb[H + q] = uw[j + H + 1 + q]; }
-            double D1, D2;
-            if constexpr (ORDER == 2) {
-                D1 = (nb[1] - nb[0]) * a.c1;
-                D2 = ((nb[1] - 2.0 * u) + nb[0]) * a.c2;
-            } else {
-                D1 = (8.0 * (nb[2] - nb[1]) - (nb[3] - nb[0])) * a.c1;
-                D2 = ((16.0 * (nb[2] + nb[1]) - 30.0 * u) - (nb[3] + nb[0])) * a.c2;
-            }
-            const double lg = lam[j];
-            const double du = 1.0 + a.dt * (a.nu * pd.g2u - (LINEAR ? 0.0 : D1));
-            double acc = lg * du;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int d = (s < H) ? -(H - s) : (s - H + 1);
-                const int i = j - d;
-                const bool same = (i >= 0 || !lo_edge) && (i < PPT || !hi_edge);
-                if (same) acc += lat(i) * Ps(s, uat(i));
-            }
-            // delayed halo contributions gathered over steps n .. n+L+m-1
-#pragma unroll
-            for (int side = 0; side < 2; ++side) {
-                const bool feeds = side == 0 ? (hi_src && j >= PPT - H) : (lo_src && j < H);
-                if (!feeds) continue;
-                const int q = side == 0 ? j - (PPT - H) : j;
-                // later levels' contributions, accumulated newest first by their
-                // producers; then this level's own (k = 0: the raw neighbour)
-                double g = gth[side][q];
-                if (knb[side] == 0)
-                    g += hweight(0, stale, 0, M) * (side == 0 ? mu_lo(q) : mu_hi(q));
-                acc += g;
-            }
-            res[j] = acc;
-            if (owns) acc_add(gacc, lg * (a.dt * D2));
-        }
-        // ---- mu^n of this tile's faces: added to the gathered sums of the
-        // earlier levels of this launch that it feeds (n-k-j, weight dH/dv_j),
-        // and to the ring for later launches
-        auto scatter = [&](int side, int q, double m) {
-            const int kk = kown[side];
-            const int need = (kk == 0 || stale) ? 1 : M;
-            for (int jw = 0; jw < need; ++jw) {
-                const int64_t nt2 = n - kk - jw;      // level this contribution belongs to
-                if (nt2 == n || nt2 < nlo) continue;  // own level: gathered directly
-                double &gref = gt[((((int)(nt2 - nlo)) * NT + tl0) * 2 + side) * H + q];
-                gref += hweight(kk, stale, jw, M) * m;
-            }
-        };
-        if (lo_edge || hi_edge) {
-            const int64_t ms = n % a.Rmu;
-#pragma unroll
-            for (int q = 0; q < H; ++q) {
-                if (lo_edge) {                        // own first h points feed the low face
-                    double m = 0.0;
-#pragma unroll
-                    for (int e = 0; e < H; ++e)
-                        if (e <= q) m += lam[e] * Ps(q - e, uc[e]);
-                    scatter(0, q, m);
-                    if (owns) a.mu[((ms * a.P + tp0) * 2 + 0) * H + q] = m;
-                }
-                if (hi_edge) {                        // own last h points feed the high face
-                    double m = 0.0;
-#pragma unroll
-                    for (int e = 0; e < H; ++e)
-                        if (e <= H - 1 - q) m += lam[PPT - 1 - e] * Ps(H + q + e, uc[PPT - 1 - e]);
-                    scatter(1, q, m);
-                    if (owns) a.mu[((ms * a.P + tp0) * 2 + 1) * H + q] = m;
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) lam[j] = res[j];
-    };
-
-    double ua[PPT], ub[PPT];
-    {
-        const double *src = a.seg + (a.nt - 1 - a.seg_n0) * a.N + gb;
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) ua[j] = src[j];
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) ub[j] = 0.0;
-    }
-    __syncthreads();                          // LDS tables ready
+    wave_sync();
     // delayed contributions to the levels of this launch from mu levels
     // written by earlier launches (nt ..), newest first; the launch's own mu
     // levels are added by their producers as they are computed
     {
         const int ng = S * NT * 2 * H;
-        for (int e = tid; e < ng; e += kThreads) {
+        for (int e = lane; e < ng; e += 64) {
             const int q = e % H;
             const int side = (e / H) & 1;
             const int tl = (e / (2 * H)) % NT;
@@ -565,25 +394,242 @@ __global__ __launch_bounds__(kThreads) void k_adj1d_fused(AdjF a)
             gt[e] = g;
         }
     }
-    int t = 0;
-    for (; t + 2 <= S; t += 2) {
-        rstep(t, ua, ub);
-        rstep(t + 1, ub, ua);
+    wave_sync();
+
+    // P_s(u) = dt*(nu*g2[s] - a*g1[s]) for a compile-time slot s
+    auto Ps = [&](int s, double u) -> double {
+        const double adv = LINEAR ? a.coef.cadv : u;
+        return dt * (nu * pd.g2[s] - adv * pd.g1[s]);
+    };
+    // region ends: no source tile in the tables
+    const bool lo_src = lo_edge && lane > 0;
+    const bool hi_src = hi_edge && lane < 63;
+    // the AT halo across this lane's faces at row `krow` (level nlo + krow) into
+    // the window's ends; contracted: the rounding of the contracted forward step
+    auto halo = [&](auto contracted, int krow, double *w) {
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            if (side == 0 ? !lo_src : !hi_src) continue;
+            const int kk = kd[(krow * NT + tl0) * 2 + side];
+            if (kk > 0) {
+                const int stl = side == 0 ? tl0 - 1 : tl0 + 1;
+#pragma unroll
+                for (int q = 0; q < H; ++q) {
+                    double vv[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                    for (int jj = 0; jj < M; ++jj)
+                        if (jj == 0 || !stale)
+                            vv[jj] = eh[((krow + DW - kk - jj) * NT + stl) * 2 * H + (1 - side) * H + q];
+                    const double hv = extrap<decltype(contracted)::value>(kk, stale, vv[0], vv[1],
+                                                                          vv[2], M);
+                    if (side == 0) w[q] = hv;
+                    else w[LAST + H + q] = hv;
+                }
+            }
+        }
+    };
+    // first and last points of the neighbouring lanes: into the places to the
+    // left and right of the lane's own points (a short lane: its last place and
+    // the one after)
+    auto around = [&](double (&w)[PPT + 2 * H]) {
+        double l[H], r[H];
+#pragma unroll
+        for (int q = 0; q < H; ++q) {
+            const double end = RAGGED ? (shrt ? w[PPT - 1 + q] : w[PPT + q]) : w[PPT + q];
+            l[q] = from_left<false>(0.0, end);
+            r[q] = from_right<false>(0.0, w[H + q]);
+        }
+#pragma unroll
+        for (int q = 0; q < H; ++q) w[q] = l[q];
+        if constexpr (RAGGED) {
+            w[H + PPT - 1] = shrt ? r[0] : w[H + PPT - 1];
+#pragma unroll
+            for (int q = 0; q < H; ++q)
+                w[H + PPT + q] = shrt ? r[q + 1 < H ? q + 1 : q] : r[q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < H; ++q) w[H + PPT + q] = r[q];
+        }
+    };
+    using exact = std::integral_constant<bool, false>;
+
+    const int mslot0 = (int)(nlo % a.Rmu);
+    Acc gacc{0.0, 0.0};                           // of all lanes; the rims' are dropped below
+    // one reverse step: level nlo + krow from lambda of the level above (lam) and
+    // its own u (uc)
+    auto rstep = [&](int krow, const double (&uc)[PPT]) {
+        // lambda and raw u of the points -H .. PPT+H-1
+        double lw[PPT + 2 * H], rw[PPT + 2 * H];
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) { lw[H + j] = lam[j]; rw[H + j] = uc[j]; }
+        around(lw);
+        around(rw);
+        // the delays and gathered sums at this level of the neighbours' faces
+        // that this lane's edge points feed
+        int kown[2] = {0, 0}, knb[2] = {1, 1};
+        double gth[2][H];
+#pragma unroll
+        for (int q = 0; q < H; ++q) { gth[0][q] = 0.0; gth[1][q] = 0.0; }
+        if (lo_edge) kown[0] = kd[(krow * NT + tl0) * 2 + 0];
+        if (hi_edge) kown[1] = kd[(krow * NT + tl0) * 2 + 1];
+        if (hi_src) {                             // feeds the next tile's low face
+            knb[0] = kd[(krow * NT + tl0 + 1) * 2 + 0];
+#pragma unroll
+            for (int q = 0; q < H; ++q) gth[0][q] = gt[((krow * NT + tl0 + 1) * 2 + 0) * H + q];
+        }
+        if (lo_src) {                             // feeds the previous tile's high face
+            knb[1] = kd[(krow * NT + tl0 - 1) * 2 + 1];
+#pragma unroll
+            for (int q = 0; q < H; ++q) gth[1][q] = gt[((krow * NT + tl0 - 1) * 2 + 1) * H + q];
+        }
+        // ---- u window with the forward AT halo across the tile faces
+        double uw[PPT + 2 * H];
+#pragma unroll
+        for (int i = 0; i < PPT + 2 * H; ++i) uw[i] = rw[i];
+        if (lo_edge || hi_edge) halo(exact{}, krow, uw);
+        // lambda and raw u at window index i (-H .. PPT+H-1), compile-time i
+        auto lat = [&](int i) -> double { return lw[H + i]; };
+        auto uat = [&](int i) -> double { return rw[H + i]; };
+        // mu^n of this step for the face a point feeds, from the raw window
+        auto mu_lo = [&](int q) -> double {         // face of the next tile, low side: its first h points
+            double m = 0.0;
+#pragma unroll
+            for (int e = 0; e < H; ++e)
+                if (e <= q) m += lat(LAST + e) * Ps(q - e, uat(LAST + e));
+            return m;
+        };
+        auto mu_hi = [&](int q) -> double {         // face of the previous tile, high side: its last h points
+            double m = 0.0;
+#pragma unroll
+            for (int e = 0; e < H; ++e)
+                if (e <= H - 1 - q) m += lat(-1 - e) * Ps(H + q + e, uat(-1 - e));
+            return m;
+        };
+        double res[PPT];
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) {
+            const double u = uc[j];
+            double nb[NS];
+#pragma unroll
+            for (int q = 0; q < H; ++q) { nb[q] = uw[j + q]; nb[H + q] = uw[j + H + 1 + q]; }
+            double D1, D2;
+            if constexpr (ORDER == 2) {
+                D1 = (nb[1] - nb[0]) * a.coef.c1;
+                D2 = ((nb[1] - 2.0 * u) + nb[0]) * a.coef.c2;
+            } else {
+                D1 = (8.0 * (nb[2] - nb[1]) - (nb[3] - nb[0])) * a.coef.c1;
+                D2 = ((16.0 * (nb[2] + nb[1]) - 30.0 * u) - (nb[3] + nb[0])) * a.coef.c2;
+            }
+            const double lg = lam[j];
+            const double du = 1.0 + dt * (nu * pd.g2u - (LINEAR ? 0.0 : D1));
+            double acc = lg * du;
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const int d = (s < H) ? -(H - s) : (s - H + 1);
+                const int i = j - d;
+                // (a neighbour in another tile: a product that is not added)
+                const bool same = (i >= 0 || !lo_edge) && (i < LAST || !hi_edge);
+                if (i >= 0 && i < LAST) acc += lat(i) * Ps(s, uat(i));
+                else if (same) acc += lat(i) * Ps(s, uat(i));
+            }
+            // delayed halo contributions gathered over steps n .. n+L+m-1
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                const bool feeds = side == 0 ? (hi_src && j >= LAST - H && j < LAST)
+                                             : (lo_src && j < H);
+                if (!feeds) continue;
+                const int q = side == 0 ? j - (LAST - H) : j;
+                // later levels' contributions, accumulated newest first by their
+                // producers; then this level's own (k = 0: the raw neighbour)
+                double g = gth[side][q];
+                if (knb[side] == 0)
+                    g += hweight(0, stale, 0, M) * (side == 0 ? mu_lo(q) : mu_hi(q));
+                acc += g;
+            }
+            res[j] = acc;
+            const double x = lg * (dt * D2);
+            acc_add_nobranch(gacc, !RAGGED || j < PPT - 1 || !shrt ? x : 0.0);
+        }
+        // ---- mu^n of this tile's faces: added to the gathered sums of the
+        // earlier levels of this launch that it feeds (n-k-j, weight dH/dv_j),
+        // and to the ring for later launches
+        auto scatter = [&](int side, int q, double m) {
+            const int kk = kown[side];
+            const int need = (kk == 0 || stale) ? 1 : M;
+            for (int jw = 0; jw < need; ++jw) {
+                const int row = krow - kk - jw;       // row of the level it belongs to
+                if (row == krow || row < 0) continue; // own level: gathered directly
+                gt[((row * NT + tl0) * 2 + side) * H + q] += hweight(kk, stale, jw, M) * m;
+            }
+        };
+        if (lo_edge || hi_edge) {
+            int ms = mslot0 + krow;
+            while (ms >= a.Rmu) ms -= a.Rmu;
+#pragma unroll
+            for (int q = 0; q < H; ++q) {
+                if (lo_edge) {                        // own first h points feed the low face
+                    double m = 0.0;
+#pragma unroll
+                    for (int e = 0; e < H; ++e)
+                        if (e <= q) m += lam[e] * Ps(q - e, uc[e]);
+                    scatter(0, q, m);
+                    if (owns) a.mu[(((int64_t)ms * a.P + tp0) * 2 + 0) * H + q] = m;
+                }
+                if (hi_edge) {                        // own last h points feed the high face
+                    double m = 0.0;
+#pragma unroll
+                    for (int e = 0; e < H; ++e)
+                        if (e <= H - 1 - q) m += lam[LAST - 1 - e] * Ps(H + q + e, uc[LAST - 1 - e]);
+                    scatter(1, q, m);
+                    if (owns) a.mu[(((int64_t)ms * a.P + tp0) * 2 + 1) * H + q] = m;
+                }
+            }
+        }
+        wave_sync();
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) lam[j] = res[j];
+    };
+    // one forward step: level nlo + krow (u) to the one above (to)
+    auto fstep = [&](int krow, const double (&u)[PPT], double (&to)[PPT]) {
+        double w[PPT + 2 * H];
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) w[H + j] = u[j];
+        around(w);
+        if (lo_edge || hi_edge) halo(std::integral_constant<bool, FMA>{}, krow, w);
+        step_window<ORDER, LINEAR, FMA, PPT>(w, a.coef);
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) to[j] = w[H + j];
+    };
+
+    // ---- groups of levels, from the top: base .. base + K - 1 (the first one
+    // may stop below; nt - S is the base of the last one)
+    double U[K][PPT], next[PPT];
+    int64_t base = a.seg_n0 + (a.nt - 1 - a.seg_n0) / K * K;
+    const auto level = [&](int64_t lev) { return a.seg + (lev - a.seg_n0) * a.N; };
+    load(level(base), next);
+    for (int count = (int)(a.nt - base); base >= nlo; base -= K, count = K) {
+        const int b = (int)(base - nlo);
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) U[0][j] = next[j];
+        if (base - K >= nlo) load(level(base - K), next);        // the next group's, in flight meanwhile
+#pragma unroll
+        for (int i = 0; i + 1 < K; ++i)
+            if (i + 1 < count) fstep(b + i, U[i], U[i + 1]);
+#pragma unroll
+        for (int i = K - 1; i >= 0; --i)
+            if (i < count) rstep(b + i, U[i]);
     }
-    if (t < S) rstep(t, ua, ub);
 
     if (owns) {
 #pragma unroll
-        for (int j = 0; j < PPT; ++j) a.lam_out[gb + j] = lam[j];
+        for (int j = 0; j < PPT; ++j)
+            if (!RAGGED || j < PPT - 1 || !shrt) a.lam_out[gb + j] = lam[j];
     }
-    __shared__ double red[kThreads / 64][2];
+    if (!owns) gacc = Acc{0.0, 0.0};
     gacc = wave_acc(gacc);
-    const int lane = tid & 63, wv = tid >> 6;
-    if (lane == 0) { red[wv][0] = gacc.s; red[wv][1] = gacc.c; }
-    __syncthreads();
-    if (tid == 0) {
+    if (lane == 0) {
         Acc Sg{a.gnu[blockIdx.x * 2], a.gnu[blockIdx.x * 2 + 1]};
-        for (int q = 0; q < kThreads / 64; ++q) acc_merge(Sg, Acc{red[q][0], red[q][1]});
+        acc_merge(Sg, gacc);
         a.gnu[blockIdx.x * 2] = Sg.s;
         a.gnu[blockIdx.x * 2 + 1] = Sg.c;
     }
@@ -593,19 +639,27 @@ __global__ __launch_bounds__(kThreads) void k_adj1d_fused(AdjF a)
 
 int adj1d_points_per_block() { return kCHA; }
 
-hipError_t launch_adj1d_fused(const AdjF &a, int order, bool linear, int ppt, int64_t nblocks,
-                              size_t lds, hipStream_t st)
+hipError_t launch_adj1d_fused(const AdjF &a, int order, bool linear, bool fma, int ppt,
+                              int64_t nblocks, size_t lds, hipStream_t st)
 {
-    dim3 grid((unsigned)nblocks), block(kThreads);
-#define AT_AF(O, LI, P) hipLaunchKernelGGL((k_adj1d_fused<O, LI, P>), grid, block, lds, st, a)
-    if (ppt != 4 && ppt != 8) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nblocks), block(64);
+#define AT_AF(O, LI, F, P, R) hipLaunchKernelGGL((k_adj1d_wave<O, LI, F, P, R>), grid, block, lds, st, a)
+#define AT_AFP(O, LI, F) do { \
+        if (a.nf == a.tpt) { if (ppt == 8) AT_AF(O, LI, F, 8, false); else AT_AF(O, LI, F, 4, false); } \
+        else if (ppt == 10) AT_AF(O, LI, F, 10, true); \
+        else if (ppt == 8) AT_AF(O, LI, F, 8, true); \
+        else if (ppt == 6) AT_AF(O, LI, F, 6, true); \
+        else AT_AF(O, LI, F, 4, true); \
+    } while (0)
+    if (ppt != 4 && ppt != 8 && (a.nf == a.tpt || (ppt != 6 && ppt != 10))) return hipErrorInvalidValue;
     if (order == 2) {
-        if (linear) { if (ppt == 8) AT_AF(2, true, 8); else AT_AF(2, true, 4); }
-        else { if (ppt == 8) AT_AF(2, false, 8); else AT_AF(2, false, 4); }
+        if (linear) { if (fma) AT_AFP(2, true, true); else AT_AFP(2, true, false); }
+        else { if (fma) AT_AFP(2, false, true); else AT_AFP(2, false, false); }
     } else {
-        if (linear) { if (ppt == 8) AT_AF(4, true, 8); else AT_AF(4, true, 4); }
-        else { if (ppt == 8) AT_AF(4, false, 8); else AT_AF(4, false, 4); }
+        if (linear) { if (fma) AT_AFP(4, true, true); else AT_AFP(4, true, false); }
+        else { if (fma) AT_AFP(4, false, true); else AT_AFP(4, false, false); }
     }
+#undef AT_AFP
 #undef AT_AF
     return hipGetLastError();
 }
@@ -614,8 +668,7 @@ size_t adj1d_fused_lds_bytes(int order, int S, int NT, int L)
 {
     const int H = order / 2, M = order == 2 ? 2 : 3;
     const size_t LV = (size_t)S + L + M - 1;
-    const size_t dbl = (size_t)2 * 2 * 2 * H * kThreads + 2 * LV * NT * 2 * H +
-                       (size_t)S * NT * 2 * H;
+    const size_t dbl = 2 * LV * NT * 2 * H + (size_t)S * NT * 2 * H;
     return 8 * dbl + ((LV * NT * 2 + 7) / 8) * 8;
 }
 

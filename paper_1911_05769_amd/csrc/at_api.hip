@@ -255,7 +255,9 @@ at_status make_layout(const at_config *c, const Derived &d, Layout &L)
         off = align_up(off + 8ull * 2 * (uint64_t)d.N);
         L.mu = off;
         off = align_up(off + 8ull * (uint64_t)L.Rmu * (uint64_t)d.P * 2 * d.h);
-        L.ngnu = (d.N + 255) / 256;   // >= the blocks of any reverse launch (chunks >= 256 points)
+        // >= the blocks of any reverse launch: chunks of at least 32 lanes of 3 or
+        // 4 points (256 points of the one-step kernel)
+        L.ngnu = (d.N + 95) / 96;
         L.gnu = off;
         off = align_up(off + 8ull * 2 * (uint64_t)L.ngnu);
     }
@@ -388,13 +390,13 @@ int whole_ppt(const at_ctx *c)
     return step1d_whole_ppt(d.N, d.W, d.P, d.order, c->cfg.L + d.m - 1);
 }
 
-// Points per thread of the launches that rebuild a checkpoint segment for the
-// adjoint: they write every level straight from registers, coalesced only for
-// few points per thread
+// Points per thread of the launches that rebuild every level of a checkpoint
+// segment for single reverse steps: they write straight from registers,
+// coalesced only for few points per thread
 constexpr int kRebuildKind = 4;
 
 at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int s, int publish,
-                    double *levels = nullptr)
+                    double *levels = nullptr, int every = 1, int levels_kind = 0)
 {
     const Derived &d = c->d;
     if (c->variant == kWholeVariant && !levels) {
@@ -432,7 +434,7 @@ at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int 
     // the fused kernels' regions, except for single steps of widths that the
     // one-step kernel takes and for the few widths the regions do not fit
     const bool plain = s == 1 && !levels && d.W % step1d_plain_points_per_thread() == 0;
-    const int want = levels ? kRebuildKind : c->kind;
+    const int want = levels ? levels_kind : c->kind;
     const FusedShape ws = plain ? FusedShape() : fused_shape(d, s, fused_kind(d, want, s));
     const Region1D rg = region_1d(d, s);
     const int reg = kThreads * rg.ppt;
@@ -456,6 +458,7 @@ at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int 
     a.slot0 = (int32_t)(n0 % a.R);
     a.D = c->cfg.L + d.m - 1;
     a.levels = levels;
+    a.levels_every = every;
     if (levels && !ws.ok) return fail(AT_ERR_STATE, "level store needs the fused kernels");
     a.nu = c->cfg.nu;
     a.dt = c->cfg.dt;
@@ -606,15 +609,9 @@ int trial_length(int trial, int s, int64_t most)
     return (int)(up <= most ? up : (trial >= s ? trial / s * s : trial));
 }
 
-// Region of a fused reverse launch of s steps (8 points per thread, aligned)
-struct RegionAdj {
-    int64_t RL, CH;
-    int NT, ppt;
-};
-
-// Points per thread of the fused reverse launches (8 or 4: the larger one
-// that still gives every SIMD four waves and divides the tile width), 0 when
-// neither divides it
+// Points per thread that adj_fuse_max's regions are measured at (8 or 4: the
+// larger one that still gives every SIMD four waves and divides the tile
+// width), 0 when neither divides it
 int adj_ppt(const Derived &d)
 {
     if (d.W % 8 == 0 && d.N >= (int64_t)4 * 1024 * 64 * 8) return 8;
@@ -622,32 +619,78 @@ int adj_ppt(const Derived &d)
     return d.W % 8 == 0 ? 8 : 0;
 }
 
-RegionAdj region_adj(const Derived &d, int s)
+// Reverse steps per launch that at_set_adjoint_fuse accepts: 0 when the tiles
+// do not fit the fused kernel, else the most (up to kMaxFuse) that keep the
+// owned chunk of a 256-thread region at least half of it (and 256 points) and
+// its LDS tables within 64 KiB.  (A launch takes as many of them as its own
+// region allows, adj_shape.)
+int adj_fuse_max(const Derived &d, int L)
 {
-    const int ppf = adj_ppt(d);
-    const int64_t reg = (int64_t)kThreads * ppf;
+    const int ppt = adj_ppt(d);
+    if (ppt == 0) return 0;
+    const int64_t reg = (int64_t)kThreads * ppt;
+    int best = 0;
+    for (int s = 1; s <= kMaxFuse; ++s) {
+        const int64_t RL = ((int64_t)s * d.h + ppt - 1) / ppt * ppt;
+        const int64_t CH = std::min<int64_t>((reg - RL - (int64_t)s * d.h) / ppt * ppt, d.N);
+        if (CH < std::min<int64_t>(std::max<int64_t>(256, reg / 2), d.N)) break;
+        const size_t lds = adj1d_fused_lds_bytes(d.order, s, (int)((reg - 1) / d.W + 2), L) +
+                           8 * (size_t)8 * d.h * kThreads;
+        if (lds > 64 * 1024) break;
+        best = s;
+    }
+    return best;
+}
+
+// The region of the fused reverse launches of S steps (a multiple of
+// kAdjGroup): one wave, rims of (S + kAdjGroup) h points, LDS tables within
+// 64 KiB; S = 0: none.
+struct RegionAdj {
+    int S = 0, ppt = 0, NT = 0, tpt = 0, nf = 0, CT = 0, RT = 0;
+    int64_t nblocks = 0;
+};
+
+RegionAdj adj_shape(const Derived &d, int L, int ppt, int s)
+{
     RegionAdj r;
-    r.ppt = ppf;
-    r.RL = ((int64_t)s * d.h + ppf - 1) / ppf * ppf;
-    r.CH = (reg - r.RL - (int64_t)s * d.h) / ppf * ppf;
-    if (r.CH > d.N) r.CH = d.N;
-    r.NT = (int)((reg - 1) / d.W + 2);
+    const int64_t tpt = (d.W + ppt - 1) / ppt, nf = d.W - tpt * (ppt - 1), nth = d.P * tpt;
+    if (nf < 1 || d.W > ((int64_t)1 << 30) || nth >= ((int64_t)1 << 31) - 256) return r;
+    if (nf == tpt && ppt != 8 && ppt != 4) return r;          // (built for ragged tiles only)
+    const int least = nf == tpt ? ppt : ppt - 1;
+    r.RT = ((s + kAdjGroup) * d.h + least - 1) / least;
+    r.NT = (int)(62 / tpt + 2);
+    if (r.RT > 16 || adj1d_fused_lds_bytes(d.order, s, r.NT, L) > 64 * 1024) return r;
+    r.S = s;
+    r.ppt = ppt;
+    r.tpt = (int)tpt;
+    r.nf = (int)nf;
+    r.CT = (int)std::min<int64_t>(64 - 2 * r.RT, nth);
+    r.nblocks = (nth + r.CT - 1) / r.CT;
     return r;
 }
 
-// Reverse steps per launch: 0 when the tiles do not fit the fused kernel,
-// else the most (up to kMaxFuse) that keep the owned chunk at least half the
-// region (and 256 points) and the LDS tables within 64 KiB
-int adj_fuse_max(const Derived &d, int L)
+// The points per thread and the most steps per launch of a sweep over segments
+// of at most `seg` steps, by an estimate of the time per step.  One wave issues
+// FP64 at nearly the rate of its SIMD and the oldest goes first, so a launch
+// takes as long as the SIMD with the most waves: 0.3 + 0.093 us per point of a
+// lane for each of them and step, and 7 us before the first.  (2^20 points,
+// order 2, us per step, waves per SIMD: 10 and 9 points 2.9 with 2, 8 points 3.4
+// with 2.4, 4 points 3.7 with 4.9.)
+RegionAdj adj_region(const Derived &d, int L, int64_t seg)
 {
-    if (adj_ppt(d) == 0) return 0;
-    int best = 0;
-    for (int s = 1; s <= kMaxFuse; ++s) {
-        const RegionAdj r = region_adj(d, s);
-        if (r.CH < std::min<int64_t>(std::max<int64_t>(256, kThreads * r.ppt / 2), d.N)) break;
-        if (adj1d_fused_lds_bytes(d.order, s, r.NT, L) > 64 * 1024) break;
-        best = s;
-    }
+    RegionAdj best;
+    double least = 0.0;
+    for (int ppt : {10, 8, 6, 4})
+        for (int s = kAdjGroup; s <= kMaxFuse; s += kAdjGroup) {
+            const RegionAdj r = adj_shape(d, L, ppt, s);
+            if (r.S == 0) break;
+            const int64_t wgs = 160 * 1024 / (int64_t)adj1d_fused_lds_bytes(d.order, s, r.NT, L);
+            const int64_t at_once = 256 * std::min<int64_t>(wgs, 4);
+            const int64_t launches = (seg + s - 1) / s;
+            const double t = (double)((r.nblocks + at_once - 1) / at_once) * (0.3 + 0.093 * ppt) +
+                             7.0 * (double)launches / (double)seg;
+            if (best.S == 0 || t < least) { best = r; least = t; }
+        }
     return best;
 }
 
@@ -1227,6 +1270,7 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
     const Derived &d = c->d;
     const int64_t nend = c->n, C = c->cfg.ckpt_every, N = d.N;
     double *lcur = c->lam, *loth = c->lam + N;
+    const RegionAdj rg = adj_region(d, c->cfg.L, std::max<int64_t>(1, std::min(C, nend)));
     AT_HIP(launch_copy(lcur, lambda_T, N, c->st));
     AT_HIP(launch_fill(c->mu, (int64_t)c->lay.Rmu * d.P * 2 * d.h, 0.0, c->st));
     AT_HIP(launch_fill(c->gnu, 2 * c->lay.ngnu, 0.0, c->st));
@@ -1234,22 +1278,35 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
         for (int64_t a0 = ((nend - 1) / C) * C; a0 >= 0; a0 -= C) {
             const int64_t a1 = std::min(a0 + C, nend);
             AT_HIP(launch_copy(c->seg, c->ckpt + (a0 / C) * N, N, c->st));
-            // rebuild levels a0+1 .. a1-1: fused launches that also store every
-            // intermediate level, or one launch per step for the tile widths the
+            // rebuild the levels the reverse launches read, every kAdjGroup-th of
+            // a0 .. a1-1 (each for single reverse steps): fused launches that store
+            // them on the way, or one launch per step for the tile widths the
             // fused kernels do not take
-            const int sr = fused_kind(d, kRebuildKind, 2) ? kMaxFuse : 1;
-            for (int64_t n = a0; n + 1 < a1;) {
-                const int s = launch_steps(d, kRebuildKind, sr, a1 - 1 - n);
+            const int smax = rg.S;
+            const int sadj = c->adj_fuse == 0 ? smax : (c->adj_fuse == 1 ? 0 : std::min(c->adj_fuse, smax));
+            const int every = sadj > 0 ? kAdjGroup : 1;
+            int kind = fused_kind(d, every == 1 ? kRebuildKind : 0, 2);
+            if (!fused_shape(d, std::max(every, 2), kind).ok) kind = 0;
+            const int64_t top = a0 + (a1 - 1 - a0) / every * every;
+            for (int64_t n = a0; n < top;) {
+                int s = 1;
+                if (kind) {
+                    s = launch_steps(d, kind, kMaxFuse, top - n);
+                    s = s < every ? every : s / every * every;
+                }
                 at_status st = launch_1d(c, c->seg + (n - a0) * N, c->seg + (n + s - a0) * N, n, s,
-                                         0, s > 1 ? c->seg + (n - a0) * N : nullptr);
+                                         0, s > 1 ? c->seg + (n - a0) * N : nullptr, every, kind);
                 if (st) return st;
                 n += s;
             }
-            const int smax = adj_fuse_max(d, c->cfg.L);
-            const int sadj = c->adj_fuse == 0 ? smax : (c->adj_fuse == 1 ? 0 : c->adj_fuse);
+            // reverse launches over whole groups of levels, from the top (the
+            // segment's last group may be short): as few as sadj allows, of even length
             for (int64_t nt = a1; sadj > 0 && nt > a0;) {
-                const int s = (int)std::min<int64_t>(sadj, nt - a0);
-                const RegionAdj rg = region_adj(d, s);
+                const int64_t groups = (nt - a0 + kAdjGroup - 1) / kAdjGroup;
+                const int64_t most = std::max(1, sadj / kAdjGroup);
+                const int64_t left = (groups + most - 1) / most;            // launches
+                const int64_t take = (groups + left - 1) / left;            // groups of this one
+                const int s = (int)(nt - a0 - (groups - take) * kAdjGroup);
                 AdjF f;
                 f.lam_in = lcur;
                 f.lam_out = loth;
@@ -1261,7 +1318,6 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
                 f.N = N;
                 f.P = d.P;
                 f.W = d.W;
-                f.CH = rg.CH;
                 f.nt = nt;
                 f.seg_n0 = a0;
                 f.nsteps_total = nend;
@@ -1269,15 +1325,21 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
                 f.Rmu = c->lay.Rmu;
                 f.L = c->cfg.L;
                 f.stale = c->cfg.halo_mode;
-                f.RL = (int32_t)rg.RL;
+                f.tpt = rg.tpt;
+                f.nf = rg.nf;
+                f.CT = rg.CT;
+                f.RT = rg.RT;
                 f.NT = rg.NT;
-                f.nu = c->cfg.nu;
-                f.dt = c->cfg.dt;
-                f.c1 = d.c1[0];
-                f.c2 = d.c2[0];
-                f.cadv = c->cfg.adv_speed;
-                const int64_t nblocks = (N + rg.CH - 1) / rg.CH;   // <= ngnu (CH >= 256)
-                AT_HIP(launch_adj1d_fused(f, d.order, c->cfg.adv_mode == 1, rg.ppt, nblocks,
+                f.coef = Step1D{};
+                f.coef.nu = c->cfg.nu;
+                f.coef.dt = c->cfg.dt;
+                f.coef.c1 = d.c1[0];
+                f.coef.c2 = d.c2[0];
+                f.coef.cadv = c->cfg.adv_speed;
+                f.coef.A1 = f.coef.dt * f.coef.c1;
+                f.coef.A2 = f.coef.dt * (f.coef.nu * f.coef.c2);
+                AT_HIP(launch_adj1d_fused(f, d.order, c->cfg.adv_mode == 1, c->cfg.arith == 1,
+                                          rg.ppt, rg.nblocks,
                                           adj1d_fused_lds_bytes(d.order, s, rg.NT, c->cfg.L),
                                           c->st));
                 std::swap(lcur, loth);

@@ -9,6 +9,7 @@ namespace atk {
 
 constexpr int kThreads = 256;     // workgroup size of every stencil kernel (4 wave64)
 constexpr int kMaxFuse = 64;      // largest steps-per-launch the ring is sized for
+constexpr int kAdjGroup = 4;      // levels the fused reverse launches recompute at a time
 constexpr int kRedBlocks = 1024;  // workgroups of the first reduction pass
 
 // Arguments of one launch of the 1D stepper: s steps n0 .. n0+s-1.
@@ -29,7 +30,9 @@ struct Step1D {
     int32_t RL;               // left rim of the loaded region (one-step kernel)
     int32_t slot0;            // n0 mod R (ring slot of level n0)
     int32_t D;                // delayed levels below n0 a step may read: L + m - 1
-    double *levels;           // optional: levels n0+1 .. n0+s-1 stored at levels + t*N (fused kernels)
+    double *levels;           // optional: every levels_every-th of the levels n0+1 .. n0+s-1
+    int32_t levels_every;     // stored, level n0+t at levels + t*N (fused kernels)
+    int32_t pad1;
     // fused regions (at_wave1d.h), in threads
     int32_t tpt, nf;          // threads per tile; those with all their points
     int32_t CT, RT;           // threads owned by a region; rim threads on each side
@@ -60,15 +63,17 @@ struct Adj1D {
 struct AdjF {
     const double *lam_in;     // lambda^{nt}
     double *lam_out;          // lambda^{nt-S}
-    const double *seg;        // u levels: level n at seg + (n - seg_n0) * N
+    const double *seg;        // u levels seg_n0, seg_n0 + kAdjGroup, ...: level n at
+                              // seg + (n - seg_n0) * N
     const double *ring;       // full edge history (record mode): [levels][P][2][h]
     double *mu;               // halo adjoints: [Rmu][P][2][h], level n in slot n mod Rmu
     const int8_t *delays;     // k[n][2P]
     double *gnu;              // per-workgroup compensated dJ/dnu: [nblocks][2]
-    int64_t N, P, W, CH;
+    int64_t N, P, W;
     int64_t nt, seg_n0, nsteps_total;
-    int32_t S, Rmu, L, stale, RL, NT;
-    double nu, dt, c1, c2, cadv;
+    int32_t S, Rmu, L, stale, NT;
+    int32_t tpt, nf, CT, RT;  // threads: of a tile, its full ones, owned, rim on each side
+    Step1D coef;              // nu, dt, c1, c2, cadv, A1, A2 of the update
 };
 
 // Weakly-synchronous 1D run (emergent delays): one workgroup per tile.
@@ -138,8 +143,8 @@ hipError_t launch_wave1d_batch(const Step1D *descs, const int2 *tbl, int64_t nbl
 hipError_t launch_adj1d(const Adj1D &a, int order, bool linear, int64_t nblocks,
                         hipStream_t st);
 int adj1d_points_per_block();
-hipError_t launch_adj1d_fused(const AdjF &a, int order, bool linear, int ppt, int64_t nblocks,
-                              size_t lds, hipStream_t st);
+hipError_t launch_adj1d_fused(const AdjF &a, int order, bool linear, bool fma, int ppt,
+                              int64_t nblocks, size_t lds, hipStream_t st);
 size_t adj1d_fused_lds_bytes(int order, int S, int NT, int L);
 bool ws1d_shape(int64_t W, int h, int *nt, int *ppt);
 int64_t ws1d_max_tiles(int order, bool linear, int64_t W);

@@ -44,6 +44,7 @@
 
 #include "at_internal.h"
 #include "at_stencil1d.h"
+#include "at_wave.h"
 
 namespace atk {
 
@@ -64,41 +65,12 @@ __host__ __device__ constexpr int wave_stage_doubles(int ppt, int nw)
     return wave_stage_pts(ppt, nw) + wave_stage_pts(ppt, nw) / ppt + (nw > 1 ? 8 * nw : 0);
 }
 
-// Lanes of a wave see each other's LDS writes in program order; this only
-// keeps the compiler from moving accesses across
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <int NW>
 __device__ __forceinline__ void region_sync()
 {
     if constexpr (NW == 1) wave_sync();
     else __syncthreads();
 }
-
-// the value of the lane to the left (lane - 1) / right (lane + 1); `end` at
-// the wave's end
-template <int CTRL, bool END>
-__device__ __forceinline__ double dpp_shift(double end, double x)
-{
-    const long long b = __double_as_longlong(x), e = __double_as_longlong(end);
-    int lo, hi;
-    if constexpr (END) {
-        lo = __builtin_amdgcn_update_dpp((int)e, (int)b, CTRL, 0xf, 0xf, false);
-        hi = __builtin_amdgcn_update_dpp((int)(e >> 32), (int)(b >> 32), CTRL, 0xf, 0xf, false);
-    } else {
-        lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
-        hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
-    }
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-template <bool END>
-__device__ __forceinline__ double from_left(double end, double x) { return dpp_shift<0x138, END>(end, x); }
-template <bool END>
-__device__ __forceinline__ double from_right(double end, double x) { return dpp_shift<0x130, END>(end, x); }
 
 template <int ORDER, bool LINEAR, bool FMA, int PPT, bool RAGGED, int NW>
 __device__ __forceinline__ void wave1d_body(const Step1D &a, const int chunk)
@@ -411,9 +383,9 @@ __device__ __forceinline__ void wave1d_body(const Step1D &a, const int chunk)
                 for (int q = 0; q < H; ++q) w[H + PPT + q] = hr[q];
             }
             step_window<ORDER, LINEAR, FMA, PPT>(w, a);
-            // every intermediate level of the owned points, straight from registers
-            // (used to rebuild a checkpoint segment for the adjoint)
-            if (STORES && a.levels && owns && t + 1 < S) {
+            // every levels_every-th intermediate level of the owned points, straight
+            // from registers (used to rebuild a checkpoint segment for the adjoint)
+            if (STORES && a.levels && owns && t + 1 < S && (t + 1) % a.levels_every == 0) {
                 double *dst = a.levels + (int64_t)(t + 1) * a.N + (int64_t)tphys * W + in_tile(ti);
 #pragma unroll
                 for (int j = 0; j < PPT; ++j)
