@@ -404,6 +404,9 @@ hipError_t launch_step1d(const Step1D &a, int order, bool linear, bool plain, bo
         const size_t xch = (size_t)kThreads * order;
         lds = 8 * (stage > xch ? stage : xch);
     }
+    // tiles of a few points with long delays ask for more than a CU's LDS (4th
+    // order, L = 4: widths below 7)
+    if (lds > 160 * 1024) return hipErrorInvalidValue;
     dim3 grid((unsigned)nblocks), block(kThreads);
 #define AT_L(K, O, LI, F) hipLaunchKernelGGL((K<O, LI, F>), grid, block, lds, st, a)
 #define AT_DISPATCH(K)                                                                   \
