@@ -212,8 +212,8 @@ at_status at_set_graph(at_ctx *ctx, int32_t use_graph);
 #define AT_DEBUG_POISON_RING 1
 at_status at_set_debug(at_ctx *ctx, int32_t flags);
 
-/* Choose the launch shape -- 1D: points per thread (the variant; 32, 16, 8 or
- * 4) together with steps per launch s, and the whole-grid variant 4 where the
+/* Choose the launch shape -- 1D: points per thread (the variant is 1, 2, 3 for
+ * 16 or 32, 8, 4; else 0) together with steps per launch s, and the whole-grid variant 4 where the
  * grid fits one workgroup; 3D:
  * the kernel variant (including the two-step variants) -- nothing that
  * changes results -- by timing about `trial_steps` steps (whole launches) from

@@ -304,13 +304,14 @@ Region1D region_1d(const Derived &d, int s)
     return r;
 }
 
-// A region of the fused kernels (at_wave1d.h) for s steps.  kind: 32, 16, 8, 4
-// are the points per thread of a one-wave region, kWide the four-wave region
-// at 16.  ok is false when the tile width is not a sum of threads of ppt and
+// A region of the fused kernels (at_wave1d.h) for s steps.  kind: the points
+// per thread (one of kFusedKinds) of a one-wave region, kWide the four-wave
+// region at 16.  ok is false when the tile width is not a sum of threads of ppt and
 // ppt - 1 points (a few widths below ppt * (ppt - 2)), when one thread is a
 // whole tile, when s is more than the rims allow, or when the LDS tables of
 // very narrow tiles exceed 64 KiB.
 constexpr int kWide = -16;
+constexpr int kFusedKinds[] = {32, 24, 20, 16, 12, 10, 8, 6, 4};
 
 struct FusedShape {
     bool ok = false;
@@ -345,26 +346,42 @@ FusedShape fused_shape(const Derived &d, int s, int kind)
     return w;
 }
 
+// Estimated time per step (us) of launches of s steps on region w.  One wave
+// issues FP64 at nearly the rate of its SIMD and the oldest goes first, so a
+// launch takes as long as the SIMD with the most waves: 0.04 + 0.0205 us per point
+// of a thread for each of them and step, 5% more for ragged threads (the others
+// have powers of two), but no less than one wave's latency; and 7 us.  Measured at
+// 1024 tiles of 1024 (us per step, points per thread x waves per SIMD), order 2:
+// 16 x 2: 0.84, 8 x 3: 0.70, 20 x 1: 0.65, 10 x 2: 0.65; order 4: 8 x 3: 1.20,
+// 12 x 2: 1.12, 20 x 1: 0.96, and with more steps per launch, so that a few SIMDs
+// have two waves, 1.51.
+double fused_cost(const Derived &d, const FusedShape &w, int s)
+{
+    const double waves = (double)((w.nblocks * w.nw + 1023) / 1024);
+    const double ragged = w.nf != w.tpt || (w.ppt & (w.ppt - 1)) != 0 ? 1.05 : 1.0;
+    const double t = std::max(0.09 + 0.0215 * w.ppt, waves * ragged * (0.04 + 0.0205 * w.ppt));
+    return t * (d.order == 4 ? 1.5 : 1.0) * (d.contracted ? 0.8 : 1.0) + 7.0 / s;
+}
+
 // The kind of region of a fused launch of s steps: the one asked for where the
-// tiles take it, else (0) by size.  In the exact order the largest grids run
-// four-wave regions (us per step with 2^24 points: 9.1, one wave: 9.8; with
-// 2^22 points one wave: 3.06).  Otherwise the most points per thread that still
-// give enough waves: at 32 points eight per SIMD (contracted, 4th order, at 32
-// and 16 points: 6.96 and 7.26 us with 2^24 grid points, 2.37 and 2.30 with
-// 2^22), below that two per SIMD (order 2 at 16, 8 and 4 points: 0.87, 0.70
-// and 1.02 us with 2^20, 0.57, 0.35 and 0.38 with 2^18).  0 when no region
-// fits this tile width.
+// tiles take it, else (0) the one of the least estimated time; 0 when no region
+// fits this tile width.  In the exact order the largest grids run four-wave
+// regions (us per step with 2^24 points: 9.1, one wave: 9.8; with 2^22 points one
+// wave: 2.9 to 3.1).
 int fused_kind(const Derived &d, int want, int s)
 {
     if (want != 0 && fused_shape(d, 1, want).ok) return want;
     if (!d.contracted && d.N >= ((int64_t)1 << 23) && s >= 32 && fused_shape(d, s, kWide).ok)
         return kWide;
     int pick = 0;
-    for (int p : {32, 16, 8, 4}) {
-        const FusedShape w = fused_shape(d, 8, p);
-        if (!w.ok) continue;
-        pick = p;
-        if (w.nblocks >= (p == 32 ? 8 : 2) * 1024) break;
+    for (int t = s; pick == 0 && t >= 1; t /= 2) {           // (s may be more than any region takes)
+        double least = 0.0;
+        for (int p : kFusedKinds) {
+            const FusedShape w = fused_shape(d, t, p);
+            if (!w.ok) continue;
+            const double cost = fused_cost(d, w, t);
+            if (pick == 0 || cost < least) { pick = p; least = cost; }
+        }
     }
     return pick;
 }
@@ -1106,16 +1123,29 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
     std::vector<std::pair<int, int>> cands;       // (points per thread or variant, steps)
     if (c->d.dim == 1) {
         const int mf = max_fuse(c);
-        for (int p : {kWide, 32, 16, 8, 4})
-            for (int s : {64, 56, 48, 40, 32, 24, 20, 16, 12, 8, 4}) {
-                if (s > mf || !fused_shape(c->d, s, p).ok) continue;
-                if (p == kWide && (s < 32 || c->d.N < ((int64_t)1 << 22))) continue;
-                cands.push_back({p, s});
+        if (c->d.N >= ((int64_t)1 << 23))
+            for (int s : {48, 64, 40, 32})
+                if (s <= mf && fused_shape(c->d, s, kWide).ok) cands.push_back({kWide, s});
+        // of each kind the most steps for each number of waves per SIMD, and a
+        // few round counts; of those the twelve of the least estimates
+        std::vector<std::pair<double, std::pair<int, int>>> est;
+        for (int p : kFusedKinds) {
+            int64_t waves = 0;
+            for (int s = std::min(mf, kMaxFuse); s >= 2; --s) {
+                const FusedShape w = fused_shape(c->d, s, p);
+                if (!w.ok) continue;
+                const int64_t now = (w.nblocks + 1023) / 1024;
+                if (now == waves && s % 16 != 0 && (s > 16 || s % 4 != 0)) continue;
+                waves = now;
+                est.push_back({fused_cost(c->d, w, s), {p, s}});
             }
+        }
+        std::sort(est.begin(), est.end());
+        for (size_t i = 0; i < est.size() && i < 12; ++i) cands.push_back(est[i].second);
         if (cands.empty())                                    // widths without such regions
             for (int s : {64, 32, 16, 8, 4})
                 if (s <= mf) cands.push_back({0, s});
-        cands.push_back({0, 1});
+        if (est.empty()) cands.push_back({0, 1});
         if (whole_ppt(c) != 0) cands.push_back({-kWholeVariant, 0});   // one launch per run
     } else {
         for (int v = 0; v < at3_variants(); ++v)
@@ -1128,8 +1158,7 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
         (void)hipEventDestroy(e0);
         return fail(AT_ERR_HIP, "at_autotune: hipEventCreate failed");
     }
-    float best_ms = 1e30f;
-    std::pair<int, int> best = cands[0];
+    std::vector<float> ms_best(cands.size(), 1e30f);
     const int keep_graph = c->use_graph;
     c->use_graph = 0;                         // time the launches themselves
     at_status st = AT_OK;
@@ -1144,21 +1173,25 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
         c->fuse = vs.second;
         if (c->d.dim == 1) {
             // the variant at_set_variant would take for this many points per
-            // thread (32 is variant 1 too), 0 where it takes none
-            const int p = std::abs(vs.first), v = p >= 16 ? 1 : (p == 8 ? 2 : (p == 4 ? 3 : 0));
+            // thread (32 is variant 1 too), 0 (by the estimate) where it takes none
+            const int p = std::abs(vs.first);
+            const int v = p == 16 || p == 32 ? 1 : (p == 8 ? 2 : (p == 4 ? 3 : 0));
             c->kind = vs.first;
             c->variant = v && c->d.W % std::min(p, 16) == 0 ? v : 0;
         }
     };
-    for (size_t i = 0; i < cands.size() && st == AT_OK; ++i) {
-        float ms_best = 1e30f;
-        choose(cands[i]);
-        const int steps = trial_length(trial_steps, c->fuse, c->cfg.nsteps_max);
-        for (int rep = 0; rep < 2 && st == AT_OK; ++rep) {
+    // twice over all candidates, not twice each: an idle device's clock takes some
+    // ten milliseconds to rise, and the first trials pay for it (2^24 points: 12.1
+    // us per step, later 9.3); then twice more over those within 5% of the best
+    for (int rep = 0; rep < 4; ++rep) {
+        const float near = 1.05f * *std::min_element(ms_best.begin(), ms_best.end());
+        for (size_t i = 0; i < cands.size() && st == AT_OK; ++i) {
+            if (rep >= 2 && ms_best[i] > near) continue;
+            choose(cands[i]);
+            const int steps = trial_length(trial_steps, c->fuse, c->cfg.nsteps_max);
             hipError_t e = clear_ring(c);
             if (e == hipSuccess) e = launch_copy(t1, u0, field_doubles(c), c->st);
             c->n = 0;
-            choose(cands[i]);
             if (e == hipSuccess) e = hipEventRecord(e0, c->st);
             if (e == hipSuccess) st = at_run(c, t1, t2, steps);
             if (e == hipSuccess && st == AT_OK) e = hipEventRecord(e1, c->st);
@@ -1167,11 +1200,14 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
             if (e == hipSuccess && st == AT_OK) e = hipEventElapsedTime(&ms, e0, e1);
             if (e != hipSuccess && st == AT_OK)
                 st = fail(AT_ERR_HIP, "at_autotune: %s", hipGetErrorString(e));
-            ms_best = std::min(ms_best, ms / (float)steps);
+            ms_best[i] = std::min(ms_best[i], ms / (float)steps);
         }
-        // the larger counts come first: a smaller one has to be 1% faster
-        if (st == AT_OK && ms_best < best_ms * 0.99f) { best_ms = ms_best; best = cands[i]; }
     }
+    // the candidates expected to be best come first: another has to be 1% faster
+    size_t pick = 0;
+    for (size_t i = 1; i < cands.size(); ++i)
+        if (ms_best[i] < ms_best[pick] * 0.99f) pick = i;
+    const std::pair<int, int> best = cands[pick];
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     c->use_graph = keep_graph;

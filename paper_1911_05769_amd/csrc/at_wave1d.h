@@ -23,7 +23,9 @@
 //     step: better only where the chip is full many times over.
 //   * Points per thread: more points share the exchange and the AT work of a
 //     step and make the rims a smaller part of the region; fewer make more
-//     waves, which a small grid needs.
+//     waves, which a small grid needs.  Between those the number of waves per
+//     SIMD decides, which is a whole number: hence kinds at 6, 10, 12, 20 and 24
+//     points too (built for ragged threads only, which any width can have).
 //   * AT halos.  What a lane at a tile face needs across it, the raw
 //     neighbour values of the levels n-1 .. n-D (D = L + m - 1), is what the
 //     exchange handed it in earlier steps; it keeps them in an LDS ring of its
@@ -35,9 +37,9 @@
 //     on a global load.
 //   * Measured against 256-thread regions that traded every thread's edges
 //     through LDS (us per step, autotuned): order 2, N = 1024: 0.74 -> 0.26,
-//     2^18: 0.70 -> 0.36, 2^20: 0.99 -> 0.71; order 4, N = 2^22: 3.45 -> 3.06,
-//     contracted 2.79 -> 2.30.  Widths that 16, 8 and 4 points do not divide
-//     had one step per launch: 999 tiles of 1001 points 20.6 -> 1.2.
+//     2^18: 0.70 -> 0.34, 2^20: 0.99 -> 0.65; order 4, N = 2^22: 3.45 -> 2.9,
+//     contracted 2.79 -> 2.2.  Widths that 16, 8 and 4 points do not divide
+//     had one step per launch: 999 tiles of 1001 points 20.6 -> 0.92.
 #pragma once
 
 #include <type_traits>
@@ -52,11 +54,17 @@ namespace {
 
 constexpr int kWave = 64;
 
-// region points a part of the LDS stage holds, 512 per wave: the field passes
-// through it in parts, so that LDS does not cap the waves per CU
+// the field passes through the LDS stage in parts of at most 640 points per
+// wave, so that LDS does not cap the waves per CU
+__host__ __device__ constexpr int wave_parts(int ppt)
+{
+    return ppt <= 10 ? 1 : (ppt <= 20 ? 2 : 4);
+}
+
+// region points of a part
 __host__ __device__ constexpr int wave_stage_pts(int ppt, int nw)
 {
-    return nw * (ppt * kWave < 512 ? ppt * kWave : 512);
+    return nw * ppt * kWave / wave_parts(ppt);
 }
 
 // the stage (one pad per PPT points), then the waves' end values [2][NW][2][2]
@@ -439,10 +447,10 @@ __device__ __forceinline__ void wave1d_body(const Step1D &a, const int chunk)
     }
 }
 
-// Waves per SIMD the registers are held to: three at 32 points (128 VGPRs
-// spilled around the loops: 10.0 against 9.6 us per step at 2^24 points), four
-// at 16, five below
-constexpr int wave_occupancy(int ppt, int nw) { return ppt >= 32 ? 3 : (ppt >= 16 && nw == 1 ? 4 : 5); }
+// Waves per SIMD the registers are held to: three at 24 and 32 points
+// (at 32, 128 VGPRs spilled around the loops: 10.0 against 9.6 us per step at
+// 2^24 points), four from 10 points, five below
+constexpr int wave_occupancy(int ppt, int nw) { return ppt >= 24 ? 3 : (ppt >= 10 && nw == 1 ? 4 : 5); }
 
 template <int ORDER, bool LINEAR, bool FMA, int PPT, bool RAGGED, int NW>
 __global__ __launch_bounds__(kWave * NW)
@@ -485,6 +493,11 @@ hipError_t launch_wave1d_order(const Step1D &a, bool linear, bool fma, int ppt, 
         if (nw == 4 && ppt == 16 && !ragged) AT_WV(LI, F, 16, false, 4);                 \
         else if (nw != 1) return hipErrorInvalidValue;                                   \
         else if (ppt == 32) AT_WR(LI, F, 32, 1);                                         \
+        else if (ppt == 24) AT_WV(LI, F, 24, true, 1);                                   \
+        else if (ppt == 20) AT_WV(LI, F, 20, true, 1);                                   \
+        else if (ppt == 12) AT_WV(LI, F, 12, true, 1);                                   \
+        else if (ppt == 10) AT_WV(LI, F, 10, true, 1);                                   \
+        else if (ppt == 6) AT_WV(LI, F, 6, true, 1);                                     \
         else if (ppt == 16) AT_WR(LI, F, 16, 1);                                         \
         else if (ppt == 8) AT_WR(LI, F, 8, 1);                                           \
         else if (ppt == 4) AT_WR(LI, F, 4, 1);                                           \

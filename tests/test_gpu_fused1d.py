@@ -103,3 +103,26 @@ def test_contracted_and_recorded(gpu, P, W):
     ref, gnu_ref = oracle.adjoint1d(u0, lam, N, P, 2, 3, nu, dt, k, nst)
     assert np.max(np.abs(g.cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(ref))
     assert abs(float(gnu) - gnu_ref) <= 1e-12 * max(abs(gnu_ref), float(np.sum(np.abs(lam))) * dt)
+
+
+# grids large enough that the estimate of a launch's time picks 6, 10, 12, 20 and
+# 24 points per thread, at tile widths that they divide and that they do not
+@pytest.mark.parametrize("P,W,order,s,arith", [
+    (256, 1024, 2, 50, 0), (260, 1002, 4, 16, 0), (1024, 1024, 2, 48, 0), (520, 2000, 2, 48, 1),
+    (512, 1024, 4, 48, 0), (900, 768, 2, 30, 0), (1024, 1024, 4, 48, 0), (999, 1001, 4, 60, 1),
+    (1024, 1000, 2, 64, 0), (4096, 1024, 4, 32, 0), (300, 4097, 4, 64, 0), (1000, 1200, 4, 48, 0)])
+def test_points_per_thread(gpu, P, W, order, s, arith):
+    print("points per thread", P, W, order, s, arith, flush=True)
+    N, nu, nst = P * W, 2e-3, s + 3                  # two launches, of different length
+    u0, dt = field(N, nu)
+    st = gpu.Stepper(n=N, p=P, order=order, L=3, nu=nu, dt=dt, nsteps_max=nst, seed=2,
+                     dist=order // 4, arith=arith)
+    u, t = dev(u0), torch.empty(N, dtype=torch.float64, device="cuda")
+    snap = st.snapshot(u)
+    got = []
+    for fuse in (1, s):
+        st.set_fuse(fuse)
+        st.restore(snap, u)
+        st.run(u, t, nst)
+        got.append(u.clone())
+    assert torch.equal(got[0], got[1])
