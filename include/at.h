@@ -160,8 +160,10 @@ at_status at_run(at_ctx *ctx, double *u, double *scratch, int64_t nsteps);
  * the AT halos of section 2, Eqs. (1)-(2)).  From step 0, arith 0, no record
  * mode.  Each tile (1D) or block (3D) is one workgroup that advances without
  * any global barrier: after each step it writes its edges / block faces into
- * the ring with device-coherent stores and then announces the level on a
- * counter; before step n it reads the neighbours' newest announced level t
+ * the ring with device-coherent stores (3D: and then announces the level on a
+ * counter; 1D: a slot whose level has not arrived holds a reserved bit pattern
+ * of a signalling NaN, and a value with just these bits is sent as a quiet
+ * one); before step n it reads the neighbours' newest level t that has arrived
  * and uses the delay k = n - min(t, n) per face, waiting only while k would
  * exceed min(L, max(0, n - m + 1)).  The delays actually used are stored in
  * the context's delay array in place of the prescribed ones (at_delays_copy
@@ -172,7 +174,7 @@ at_status at_run(at_ctx *ctx, double *u, double *scratch, int64_t nsteps);
  *   jitter     0: none; J > 0: before each step a tile idles a pseudo-random
  *              0..J units of about 128 clocks (hash of seed, tile, step),
  *              emulating uneven arrival
- *   spin_limit polls of a counter before a wait gives up (<= 0: 2^20)
+ *   spin_limit polls of a counter (1D: of the ring slots) before a wait gives up (<= 0: 2^20)
  * Requirements: 1D: tile width W = 256 q or 64 q with q in {1, 2, 4, 8, 16}
  * (q >= 2 for order 4; one workgroup of 256 threads, or of one wave, per
  * tile); 3D: block widths multiples of 64 (x) and 8 (y).  All tiles or
@@ -353,9 +355,10 @@ at_status at_batch_set_fuse(at_batch *b, int32_t fuse_steps);
 at_status at_set_fuse(at_ctx *ctx, int32_t fuse_steps);
 
 /* Reverse steps per launch of at_adjoint.  0 (default): as many as the grid
- * allows (fused reverse launches need a tile width that is a multiple of 4,
- * else one step per launch); 1: one reverse step per launch; 2..64: at most
- * that many per launch (AT_ERR_ARG beyond this grid's limit).  Every setting
+ * allows (tiles of a few points: one per launch); 1: one reverse step per
+ * launch; 2..64: at most that many per launch, in whole groups of 4 (AT_ERR_ARG
+ * beyond this grid's limit, and for tile widths that are no multiple of 4).
+ * Every setting
  * gives the same lambda bits; dJ/dnu is summed in a different grouping. */
 at_status at_set_adjoint_fuse(at_ctx *ctx, int32_t steps);
 
