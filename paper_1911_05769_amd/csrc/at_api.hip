@@ -1188,7 +1188,9 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
         for (size_t i = 0; i < cands.size() && st == AT_OK; ++i) {
             if (rep >= 2 && ms_best[i] > near) continue;
             choose(cands[i]);
-            const int steps = trial_length(trial_steps, c->fuse, c->cfg.nsteps_max);
+            // (a run of the whole-grid variant is one launch, whatever its length)
+            const int s = c->d.dim == 1 && c->variant == kWholeVariant ? kMaxFuse : c->fuse;
+            const int steps = trial_length(trial_steps, s, c->cfg.nsteps_max);
             hipError_t e = clear_ring(c);
             if (e == hipSuccess) e = launch_copy(t1, u0, field_doubles(c), c->st);
             c->n = 0;

@@ -23,13 +23,11 @@ namespace {
 
 constexpr int kWT = 256;      // threads of the workgroup
 
-// ring slot of level n0 + d (|d| < R)
+// ring slot of level n0 + d (-R <= d < 0)
 __device__ __forceinline__ int64_t wslot(const Step1D &a, int64_t d)
 {
-    int64_t x = a.slot0 + d;
-    if (x < 0) x += a.R;
-    if (x >= a.R) x -= a.R;
-    return x;
+    const int64_t x = a.slot0 + d;
+    return x < 0 ? x + a.R : x;
 }
 
 template <int ORDER, bool LINEAR, bool FMA, int PPT>
@@ -75,7 +73,11 @@ __global__ __launch_bounds__(kWT) void k_step1d_whole(Step1D a)
     if (hi_edge && S > 0) kr = a.delays[a.n0 * F + 2 * tile + 1];
     __syncthreads();
 
-    for (int t = 0, tb = 0; t < S; ++t, tb = (tb + 1 == HR) ? 0 : tb + 1) {
+    // tb: t mod HR; slot: the ring slot of level n0 + t (a launch may go around
+    // the ring any number of times)
+    int slot = a.slot0;
+    for (int t = 0, tb = 0; t < S;
+         ++t, tb = (tb + 1 == HR) ? 0 : tb + 1, slot = (slot + 1 == a.R) ? 0 : slot + 1) {
         const int64_t n = a.n0 + t;
         int kl2 = 0, kr2 = 0;
         if (t + 1 < S) {
@@ -87,16 +89,15 @@ __global__ __launch_bounds__(kWT) void k_step1d_whole(Step1D a)
         if (lo_edge || hi_edge) {
             const int row = hrow(tb + D);
             const bool pub = a.publish == 1 || (a.publish == 2 && t + D >= S);
-            const int64_t slot = wslot(a, t);
 #pragma unroll
             for (int q = 0; q < H; ++q) {
                 if (lo_edge) {
                     eh[((row * P + tile) * 2 + 0) * H + q] = w[H + q];
-                    if (pub) a.ring[((slot * a.P + tile) * 2 + 0) * H + q] = w[H + q];
+                    if (pub) a.ring[(((int64_t)slot * a.P + tile) * 2 + 0) * H + q] = w[H + q];
                 }
                 if (hi_edge) {
                     eh[((row * P + tile) * 2 + 1) * H + q] = w[PPT + q];
-                    if (pub) a.ring[((slot * a.P + tile) * 2 + 1) * H + q] = w[PPT + q];
+                    if (pub) a.ring[(((int64_t)slot * a.P + tile) * 2 + 1) * H + q] = w[PPT + q];
                 }
             }
         }
