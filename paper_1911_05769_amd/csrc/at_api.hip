@@ -627,13 +627,15 @@ void drop_graph(at_ctx *c)
     c->g_n0 = c->g_nsteps = -1;
 }
 
-// Steps of a tuning trial: whole launches of the candidate's s steps, compared
-// per step (a run splits its steps evenly over its launches, so a trial of the
+// Steps of a tuning trial: whole launches of the candidate's s steps, an even
+// number of them where the run allows it, compared per step (a run splits its
+// steps evenly over its launches and prefers an even number, so a trial of the
 // same length for all would make candidates alike)
 int trial_length(int trial, int s, int64_t most)
 {
-    const int64_t up = ((int64_t)trial + s - 1) / s * s;
-    return (int)(up <= most ? up : (trial >= s ? trial / s * s : trial));
+    const int64_t n = ((int64_t)trial + s - 1) / s, pairs = (n + 1) / 2 * 2 * s;
+    if (pairs <= most) return (int)pairs;
+    return (int)(n * s <= most ? n * s : (trial >= s ? trial / s * s : trial));
 }
 
 // Points per thread that adj_fuse_max's regions are measured at (8 or 4: the

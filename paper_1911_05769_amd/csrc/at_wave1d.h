@@ -447,14 +447,17 @@ __device__ __forceinline__ void wave1d_body(const Step1D &a, const int chunk)
     }
 }
 
-// Waves per SIMD the registers are held to: three at 24 and 32 points
-// (at 32, 128 VGPRs spilled around the loops: 10.0 against 9.6 us per step at
-// 2^24 points), four from 10 points, five below
-constexpr int wave_occupancy(int ppt, int nw) { return ppt >= 24 ? 3 : (ppt >= 10 && nw == 1 ? 4 : 5); }
+// Waves per SIMD the registers are held to: three at 24 and 32 points (at 32,
+// 128 VGPRs spilled around the loops: 10.0 against 9.6 us per step at 2^24
+// points; two, without any spill, 5.58 against 5.43 ms for a batch), four from 10
+// points (four-wave regions held to five spilled 36 VGPRs around the loops, 117 MB
+// of scratch written per launch of 2^24 points: 9.26 against 9.03 us per step),
+// five below
+constexpr int wave_occupancy(int ppt) { return ppt >= 24 ? 3 : (ppt >= 10 ? 4 : 5); }
 
 template <int ORDER, bool LINEAR, bool FMA, int PPT, bool RAGGED, int NW>
 __global__ __launch_bounds__(kWave * NW)
-__attribute__((amdgpu_waves_per_eu(wave_occupancy(PPT, NW))))
+__attribute__((amdgpu_waves_per_eu(wave_occupancy(PPT))))
 void k_wave1d(Step1D a)
 {
     wave1d_body<ORDER, LINEAR, FMA, PPT, RAGGED, NW>(a, blockIdx.x);
@@ -465,7 +468,7 @@ void k_wave1d(Step1D a)
 // coefficients; flip = 1 swaps the field pointers (ping-pong launches).
 template <int ORDER, bool LINEAR, bool FMA, int PPT, int NW>
 __global__ __launch_bounds__(kWave * NW)
-__attribute__((amdgpu_waves_per_eu(wave_occupancy(PPT, NW))))
+__attribute__((amdgpu_waves_per_eu(wave_occupancy(PPT))))
 void k_wave1d_batch(const Step1D *descs, const int2 *tbl, int64_t n0, int flip)
 {
     const int2 e = tbl[blockIdx.x];
