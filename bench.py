@@ -36,7 +36,8 @@ METRIC = "grid-point updates/s & % HBM peak (AT step, adjoint, batched) vs plain
 # (bytes_per_launch None) until they have been taken on the current source.
 TRAFFIC = {"sources": ["paper_1911_05769_amd/csrc/at_wave1d.h",
                        "paper_1911_05769_amd/csrc/at_stencil1d.h"],
-           "md5": None, "fuse": 56, "bytes_per_launch": None}
+           "md5": "edb2b503c6127514aee30e3e7c09af49", "fuse": 48,
+           "bytes_per_launch": 73248.6 * 1024 * 2.0 + 132608 * 1024}
 
 
 def eprint(*a):
@@ -538,10 +539,10 @@ def bench_adjoint(args, torch, at, I):
     tf = min(t[0] for t in times)
     ta = min(t[1] for t in times)
     pstep = N * nst
-    # reverse sweep, algorithmic floor: every intermediate level of u is written
-    # once by the recompute and read once by the reverse steps (16 B per
-    # point-step); lambda stays on chip within a fused reverse launch
-    gbps = pstep * 16.0 / ta / 1e9
+    # reverse sweep, algorithmic floor: every fourth level of u is written once by
+    # the rebuild and read once by the reverse launches (4 B per point-step); the
+    # other levels and lambda stay on chip within a fused reverse launch
+    gbps = pstep * 4.0 / ta / 1e9
     eprint("[adjoint] forward %.2f ms, adjoint %.2f ms (%.0f GB/s algorithmic), J %.3e, "
            "dJ/dnu %.4e" % (tf * 1e3, ta * 1e3, gbps, float(J), float(gnu)))
     return {"value": pstep / (tf + ta), "unit": "point-steps/s (gradient)",
