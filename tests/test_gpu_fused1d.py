@@ -126,3 +126,32 @@ def test_points_per_thread(gpu, P, W, order, s, arith):
         st.run(u, t, nst)
         got.append(u.clone())
     assert torch.equal(got[0], got[1])
+
+
+# runs on large grids take one launch more where their number would be odd, so
+# that the last one writes the caller's field; a run of one step copies
+@pytest.mark.parametrize("steps,fuse", [(1, 8), (2, 8), (7, 8), (20, 8), (24, 8), (50, 20), (61, 20), (3, 1)])
+def test_even_number_of_launches(gpu, steps, fuse):
+    print("even launches", steps, fuse, flush=True)
+    N, P, nu = 1 << 21, 2048, 2e-3
+    u0, dt = field(N, nu)
+    st = gpu.Stepper(n=N, p=P, order=2, L=3, nu=nu, dt=dt, nsteps_max=2 * steps, seed=4)
+    snap, got = st.snapshot(dev(u0)), []
+    for f in (1, fuse):
+        u, t = torch.empty(N, dtype=torch.float64, device="cuda"), torch.empty(N, dtype=torch.float64, device="cuda")
+        st.set_fuse(f)
+        st.restore(snap, u)
+        if f == 1:
+            for _ in range(2 * steps):
+                st.step(u, t)
+                u, t = t, u
+        else:
+            st.run(u, t, steps)
+            st.run(u, t, steps)
+        got.append(u)
+    if fuse > 1:
+        assert torch.equal(got[0], got[1])
+    else:
+        st.restore(snap, got[1])
+        st.run(got[1], t, 2 * steps)
+        assert torch.equal(got[0], got[1])
