@@ -104,6 +104,7 @@ Div31 make_div31(uint32_t d)
 // The work order of k_step3d_point
 struct Point3D {
     uint32_t total, per;      // workgroups; an XCD's share of them
+    uint32_t first;           // of this launch, in the order they are dealt to the XCDs
     uint32_t strip_wgs, plane_wgs;   // of a strip; of one plane of a strip
     int32_t rows;             // rows of a strip
     Div31 dnx, dWx, dWy;
@@ -143,7 +144,8 @@ __global__ __launch_bounds__(kPointThreads) void k_step3d_point(Step3D A, Point3
 {
     const int nx = (int)A.nx, ny = (int)A.ny, nz = (int)A.nz;
     // ---- this workgroup's place in the order, its plane and strip (uniform)
-    const unsigned wid = (blockIdx.x % 8) * G.per + blockIdx.x / 8;
+    const unsigned dealt = G.first + blockIdx.x;
+    const unsigned wid = (dealt % 8) * G.per + dealt / 8;
     if (wid >= G.total) return;
     const unsigned strip = wid / G.strip_wgs, in_strip = wid - strip * G.strip_wgs;
     const int z = (int)(in_strip / G.plane_wgs);
@@ -1538,25 +1540,31 @@ static at_status at3_launch_point(at_ctx *ctx, const Step3D &A)
     G.rows = (int32_t)(rows < A.ny ? rows : A.ny);
     G.plane_wgs = (uint32_t)((G.rows * A.nx + kPointThreads - 1) / kPointThreads);
     const int64_t strips = (A.ny + G.rows - 1) / G.rows;
-    const int64_t total = strips * A.nz * G.plane_wgs;      // < 2^31 points / 256 x 2
+    const int64_t total = strips * A.nz * G.plane_wgs;      // < 2^30 (a plane has at least 4 points)
     G.strip_wgs = (uint32_t)(A.nz * G.plane_wgs);
     G.total = (uint32_t)total;
     G.per = (uint32_t)((total + 7) / 8);
     G.dnx = make_div31((uint32_t)A.nx);
     G.dWx = make_div31((uint32_t)A.Wx);
     G.dWy = make_div31((uint32_t)A.Wy);
-    const dim3 grid(8 * G.per), block(kPointThreads);
+    // A launch holds fewer than 2^32 threads: a box of 2^24 planes or more (of at
+    // least one workgroup each) takes several
+    constexpr uint32_t kMost = (uint32_t)1 << 23;     // workgroups of a launch (a multiple of 8)
+    const dim3 block(kPointThreads);
     hipStream_t st = at_ctx_stream(ctx);
-    switch (A.nc) {
-    case 3: hipLaunchKernelGGL(k_step3d_point<3>, grid, block, 0, st, A, G); break;
-    case 4: hipLaunchKernelGGL(k_step3d_point<4>, grid, block, 0, st, A, G); break;
-    case 5: hipLaunchKernelGGL(k_step3d_point<5>, grid, block, 0, st, A, G); break;
-    case 6: hipLaunchKernelGGL(k_step3d_point<6>, grid, block, 0, st, A, G); break;
-    case 7: hipLaunchKernelGGL(k_step3d_point<7>, grid, block, 0, st, A, G); break;
-    default: return at_fail(AT_ERR_ARG, "no 3D build for this component count");
+    for (G.first = 0; G.first < 8 * G.per; G.first += kMost) {
+        const dim3 grid(std::min(kMost, 8 * G.per - G.first));
+        switch (A.nc) {
+        case 3: hipLaunchKernelGGL(k_step3d_point<3>, grid, block, 0, st, A, G); break;
+        case 4: hipLaunchKernelGGL(k_step3d_point<4>, grid, block, 0, st, A, G); break;
+        case 5: hipLaunchKernelGGL(k_step3d_point<5>, grid, block, 0, st, A, G); break;
+        case 6: hipLaunchKernelGGL(k_step3d_point<6>, grid, block, 0, st, A, G); break;
+        case 7: hipLaunchKernelGGL(k_step3d_point<7>, grid, block, 0, st, A, G); break;
+        default: return at_fail(AT_ERR_ARG, "no 3D build for this component count");
+        }
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return at_fail(AT_ERR_HIP, hipGetErrorString(e));
     }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return at_fail(AT_ERR_HIP, hipGetErrorString(e));
     return AT_OK;
 }
 
@@ -1627,6 +1635,8 @@ static bool at3_launch_brick(at_ctx *ctx, const Step3D &A)
     G.dey = make_div31((uint32_t)G.ey);
     G.dex1 = make_div31((uint32_t)(A.Wx - (G.nbx - 1) * G.ex));
     G.dey1 = make_div31((uint32_t)(A.Wy - (G.nby - 1) * G.ey));
+    // (a launch holds fewer than 2^32 threads)
+    if ((uint64_t)8 * G.per * (uint64_t)(G.ex * G.ey * G.kz) >= (uint64_t)1 << 32) return false;
     const dim3 grid(8 * G.per), block((unsigned)(G.ex * G.ey * G.kz));
     const size_t lds = (size_t)(G.ex + 2) * (G.ey + 2) * (G.ez + 2) * A.nc * 8;
     hipStream_t st = at_ctx_stream(ctx);
