@@ -267,9 +267,20 @@ at_status make_layout(const at_config *c, const Derived &d, Layout &L)
 
 Region1D region_1d(const Derived &d, int s);
 
-// Largest steps-per-launch usable for this 1D configuration: the owned chunk
-// stays at least half the region (or the whole grid) and the LDS edge
-// history fits in 64 KiB.
+// The most steps per launch at_set_fuse accepts, a limit of the interface: in a
+// region of 256 threads the owned chunk stays at least half of it (or the whole
+// grid), and a table of its tile edges over the s steps and the D = L + m - 1
+// levels below fits 64 KiB beside the field's stage.  (On tiles of a few dozen
+// points the fused kernels' own regions would take more: order 4, L = 4: 6 here
+// at 33 points, 40 there.)
+size_t edge_table_bytes(const Derived &d, int s, int NT, int ppt)
+{
+    const size_t stage = (size_t)kThreads * (ppt + 1) / (ppt >= 16 ? 2 : 1);
+    const size_t xch = (size_t)2 * kThreads * d.order;
+    const size_t edges = (size_t)(d.L + d.m - 1 + s - 1) * NT * d.order;
+    return 8 * (std::max(stage, xch) + edges + ((size_t)s * NT * 2 + 7) / 8);
+}
+
 int max_fuse_1d(const Derived &d)
 {
     int best = 1;
@@ -278,7 +289,7 @@ int max_fuse_1d(const Derived &d)
         const int reg = kThreads * rg.ppt;
         if (rg.CH < std::min<int64_t>(reg / 2, d.N)) break;
         const int NT = (int)((reg - 1) / d.W + 2);
-        if (step1d_lds_bytes(d.order, s, NT, d.L + d.m - 1, rg.ppt) > 64 * 1024) break;
+        if (edge_table_bytes(d, s, NT, rg.ppt) > 64 * 1024) break;
         best = s;
     }
     return best;

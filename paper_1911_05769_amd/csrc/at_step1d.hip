@@ -32,6 +32,8 @@
 //   * owned tile-edge points are published to ring slot n mod R: those of every
 //     level when the run keeps the edge tape for the adjoint, else those of the
 //     last L + m - 1 levels of a launch, the only ones a later launch reads.
+#include <algorithm>
+
 #include "at_internal.h"
 #include "at_stencil1d.h"
 
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(kThreads) void k_step1d(Step1D a)
     extern __shared__ double lds[];
     double *stage = lds;                                  // one part of the stage (load_window)
     double *xch = lds;                                    // [2][kThreads][2H]  (aliases stage)
-    double *eh = lds + 2 * kThreads * 2 * H;              // [D+s-1][NT][2][H]  (aliases stage)
+    double *eh = lds + 2 * kThreads * 2 * H;              // [s-1][NT][2][H]  (aliases stage)
 
     const int tid = threadIdx.x;
     const int64_t c0 = (int64_t)blockIdx.x * a.CH;
@@ -382,15 +384,14 @@ __global__ __launch_bounds__(kThreads) void k_step1d_plain(Step1D a)
 int step1d_points_per_thread() { return kPPT; }
 int step1d_plain_points_per_thread() { return kPPTPlain; }
 
-// LDS of k_step1d: the stage part or the exchange buffers, then the edge
-// history of the launch's levels
-size_t step1d_lds_bytes(int order, int s, int NT, int D, int ppt)
+// LDS of k_step1d: the stage part, or the exchange buffers and behind them the
+// edges of the levels that later steps of the launch read (none in a launch of
+// one step: the levels below n0 and the delays are read from memory)
+static size_t step1d_lds_bytes(int order, int s, int NT)
 {
-    const int H = order / 2;
-    const size_t stage = (size_t)stage_doubles(ppt);
-    const size_t xch = (size_t)2 * kThreads * 2 * H;
-    const size_t hist = (size_t)(D + s - 1) * NT * 2 * H + ((size_t)s * NT * 2 + 7) / 8;
-    return 8 * ((stage > xch ? stage : xch) + hist);
+    const size_t stage = (size_t)stage_doubles(kPPT);
+    const size_t xch = (size_t)2 * kThreads * order, hist = (size_t)(s - 1) * NT * order;
+    return 8 * std::max(stage, xch + hist);
 }
 
 // k_step1d_plain where plain (one step, tile widths multiples of 8), else the
@@ -398,14 +399,12 @@ size_t step1d_lds_bytes(int order, int s, int NT, int D, int ppt)
 hipError_t launch_step1d(const Step1D &a, int order, bool linear, bool plain, bool fma,
                          int64_t nblocks, hipStream_t st)
 {
-    size_t lds = step1d_lds_bytes(order, a.s, a.NT, a.D, kPPT);
+    size_t lds = step1d_lds_bytes(order, a.s, a.NT);
     if (plain) {
         const size_t stage = (size_t)stage_doubles(kPPTPlain);
         const size_t xch = (size_t)kThreads * order;
         lds = 8 * (stage > xch ? stage : xch);
     }
-    // tiles of a few points with long delays ask for more than a CU's LDS (4th
-    // order, L = 4: widths below 7)
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     dim3 grid((unsigned)nblocks), block(kThreads);
 #define AT_L(K, O, LI, F) hipLaunchKernelGGL((K<O, LI, F>), grid, block, lds, st, a)
