@@ -297,10 +297,9 @@ int max_fuse_1d(const Derived &d)
 
 Region1D region_1d(const Derived &d, int s)
 {
-    // single steps use the 8-point-per-thread kernel when the tiles allow it
-    const int pplain = step1d_plain_points_per_thread();
-    const bool plain = s == 1 && d.W % pplain == 0;
-    const int ppt = plain ? pplain : (d.W % d.fppt == 0 ? d.fppt : step1d_points_per_thread());
+    // single steps use the one-step kernel when the tiles allow it
+    const int plain = s == 1 ? step1d_plain_ppt(d.W) : 0;
+    const int ppt = plain ? plain : (d.W % d.fppt == 0 ? d.fppt : step1d_points_per_thread());
     const int64_t reg = (int64_t)kThreads * ppt;
     Region1D r;
     r.ppt = ppt;
@@ -471,7 +470,7 @@ at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int 
     }
     // the fused kernels' regions, except for single steps of widths that the
     // one-step kernel takes and for the few widths the regions do not fit
-    const bool plain = s == 1 && !levels && d.W % step1d_plain_points_per_thread() == 0;
+    const int plain = s == 1 && !levels ? step1d_plain_ppt(d.W) : 0;
     const int want = levels ? levels_kind : c->kind;
     const FusedShape ws = plain ? FusedShape() : fused_shape(d, s, fused_kind(d, want, s));
     const Region1D rg = region_1d(d, s);

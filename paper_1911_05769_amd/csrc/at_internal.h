@@ -126,8 +126,8 @@ hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t st);
 hipError_t launch_poison(double *ring, int64_t R, int64_t lev, int s0, int nlive, hipStream_t st);
 hipError_t launch_copy(double *dst, const double *src, int64_t n, hipStream_t st);
 int step1d_points_per_thread();
-int step1d_plain_points_per_thread();
-hipError_t launch_step1d(const Step1D &a, int order, bool linear, bool plain, bool fma,
+int step1d_plain_ppt(int64_t W);
+hipError_t launch_step1d(const Step1D &a, int order, bool linear, int plain_ppt, bool fma,
                          int64_t nblocks, hipStream_t st);
 size_t step1d_whole_lds_bytes(int order, int64_t P, int D);
 int step1d_whole_ppt(int64_t N, int64_t W, int64_t P, int order, int D);

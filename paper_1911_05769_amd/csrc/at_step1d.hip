@@ -42,7 +42,6 @@ namespace atk {
 namespace {
 
 constexpr int kPPT = 16;      // region points per thread (general kernel)
-constexpr int kPPTPlain = 8;  // region points per thread of the single-step kernel
 
 __device__ __forceinline__ int64_t floordiv(int64_t a, int64_t b)
 {
@@ -295,18 +294,21 @@ __global__ __launch_bounds__(kThreads) void k_step1d(Step1D a)
 
 
 // One step per launch (the plain form), for tile widths that are multiples of
-// PPT = 8: every thread's points lie in one tile.  A thread that starts a tile
-// writes its left AT halo values into the left part of its register window, a
-// thread that ends a tile its right ones, and then every point runs the same
-// stencil (the split of section 5.2).  HBM-bound: 6.2 TB/s of 16 bytes per
-// point at 2^24 points; 8 points per thread keep the workgroup small and more
-// of them in flight than 16.
-template <int ORDER, bool LINEAR, bool FMA>
+// PPT (8, else 4): every thread's points lie in one tile.  A thread that starts
+// a tile writes its left AT halo values into the left part of its register
+// window, a thread that ends a tile its right ones, and then every point runs
+// the same stencil (the split of section 5.2).  HBM-bound: 6.2 TB/s of 16 bytes
+// per point at 2^24 points; 8 points per thread keep the workgroup small and
+// more of them in flight than 16.  Grids that the caches hold are bound by the
+// trips to memory of a wave with a face: field, delay, ring, the ring once for
+// both sides (order 4, 2^22 points, us per step, one side after the other and
+// together: tiles of 4096 14.2 and 12.8, of 64 18.5 and 16.3).  100000 tiles of 12
+// points: 14.2 as a launch of the fused kernels with all their history, 7.7 here.
+template <int ORDER, bool LINEAR, bool FMA, int PPT>
 __global__ __launch_bounds__(kThreads) void k_step1d_plain(Step1D a)
 {
     constexpr int H = ORDER / 2;
     constexpr int M = (ORDER == 2) ? 2 : 3;
-    constexpr int PPT = kPPTPlain;
     extern __shared__ double lds[];
     double *stage = lds;                                  // one part of the stage (load_window)
     double *xch = lds;                                    // [kThreads][2H]  (aliases stage)
@@ -356,22 +358,28 @@ __global__ __launch_bounds__(kThreads) void k_step1d_plain(Step1D a)
     // ---- AT halo approximation at tile edges (k = 0: the raw neighbour stays)
     if (lo_edge || hi_edge) {
         const int8_t *krow = a.delays + a.n0 * (2 * a.P) + 2 * tp0;
-        const int kk[2] = {lo_edge && tid > 0 ? krow[0] : 0, hi_edge ? krow[1] : 0};
-        const int64_t src[2] = {2 * (tp0 == 0 ? a.P - 1 : tp0 - 1) + 1,
-                                2 * (tp0 == a.P - 1 ? 0 : tp0 + 1)};
+        const int kl = lo_edge && tid > 0 ? krow[0] : 0, kr = hi_edge ? krow[1] : 0;
+        // the lanes that start a tile and those that end one in the same pass, one
+        // trip to the ring for both; a lane that does both (a tile of PPT points)
+        // takes its right halo in a second one
+        const bool both = lo_edge && hi_edge;
 #pragma unroll
-        for (int side = 0; side < 2; ++side) {
-            if (kk[side] == 0) continue;
+        for (int pass = 0; pass < 2; ++pass) {
+            const bool left = pass == 0 && lo_edge;
+            const int kk = pass == 0 ? (lo_edge ? kl : kr) : (both ? kr : 0);
+            if (kk == 0) continue;
+            const int64_t src = left ? 2 * (tp0 == 0 ? a.P - 1 : tp0 - 1) + 1
+                                     : 2 * (tp0 == a.P - 1 ? 0 : tp0 + 1);
 #pragma unroll
             for (int q = 0; q < H; ++q) {
                 double vv[3] = {0.0, 0.0, 0.0};
 #pragma unroll
                 for (int jj = 0; jj < M; ++jj)
                     if (jj == 0 || !a.stale)
-                        vv[jj] = a.ring[(ring_slot(a, -kk[side] - jj) * a.P * 2 + src[side]) * H + q];
-                const double hv = extrap<FMA>(kk[side], a.stale != 0, vv[0], vv[1], vv[2], M);
-                if (side == 0) w[q] = hv;
-                else w[PPT + H + q] = hv;
+                        vv[jj] = a.ring[(ring_slot(a, -kk - jj) * a.P * 2 + src) * H + q];
+                const double hv = extrap<FMA>(kk, a.stale != 0, vv[0], vv[1], vv[2], M);
+                w[q] = left ? hv : w[q];
+                w[PPT + H + q] = left ? w[PPT + H + q] : hv;
             }
         }
     }
@@ -382,7 +390,9 @@ __global__ __launch_bounds__(kThreads) void k_step1d_plain(Step1D a)
 }  // namespace
 
 int step1d_points_per_thread() { return kPPT; }
-int step1d_plain_points_per_thread() { return kPPTPlain; }
+
+// points per thread of k_step1d_plain at tile width W, 0: it does not take it
+int step1d_plain_ppt(int64_t W) { return W % 8 == 0 ? 8 : (W % 4 == 0 ? 4 : 0); }
 
 // LDS of k_step1d: the stage part, or the exchange buffers and behind them the
 // edges of the levels that later steps of the launch read (none in a launch of
@@ -394,33 +404,30 @@ static size_t step1d_lds_bytes(int order, int s, int NT)
     return 8 * std::max(stage, xch + hist);
 }
 
-// k_step1d_plain where plain (one step, tile widths multiples of 8), else the
-// general k_step1d
-hipError_t launch_step1d(const Step1D &a, int order, bool linear, bool plain, bool fma,
+// k_step1d_plain of plain_ppt points per thread (one step), or (0) the general k_step1d
+hipError_t launch_step1d(const Step1D &a, int order, bool linear, int plain_ppt, bool fma,
                          int64_t nblocks, hipStream_t st)
 {
     size_t lds = step1d_lds_bytes(order, a.s, a.NT);
-    if (plain) {
-        const size_t stage = (size_t)stage_doubles(kPPTPlain);
-        const size_t xch = (size_t)kThreads * order;
-        lds = 8 * (stage > xch ? stage : xch);
+    if (plain_ppt) {
+        const size_t stage = (size_t)stage_doubles(plain_ppt), xch = (size_t)kThreads * order;
+        lds = 8 * std::max(stage, xch);
     }
     if (lds > 160 * 1024) return hipErrorInvalidValue;
     dim3 grid((unsigned)nblocks), block(kThreads);
-#define AT_L(K, O, LI, F) hipLaunchKernelGGL((K<O, LI, F>), grid, block, lds, st, a)
-#define AT_DISPATCH(K)                                                                   \
-    do {                                                                                 \
-        if (order == 2) {                                                                \
-            if (linear) { if (fma) AT_L(K, 2, true, true); else AT_L(K, 2, true, false); } \
-            else { if (fma) AT_L(K, 2, false, true); else AT_L(K, 2, false, false); }    \
-        } else {                                                                         \
-            if (linear) { if (fma) AT_L(K, 4, true, true); else AT_L(K, 4, true, false); } \
-            else { if (fma) AT_L(K, 4, false, true); else AT_L(K, 4, false, false); }    \
-        }                                                                                \
+#define AT_L(O, LI, F)                                                                    \
+    do {                                                                                  \
+        if (plain_ppt == 8) hipLaunchKernelGGL((k_step1d_plain<O, LI, F, 8>), grid, block, lds, st, a); \
+        else if (plain_ppt == 4) hipLaunchKernelGGL((k_step1d_plain<O, LI, F, 4>), grid, block, lds, st, a); \
+        else hipLaunchKernelGGL((k_step1d<O, LI, F>), grid, block, lds, st, a);           \
     } while (0)
-    if (plain) AT_DISPATCH(k_step1d_plain);
-    else AT_DISPATCH(k_step1d);
-#undef AT_DISPATCH
+    if (order == 2) {
+        if (linear) { if (fma) AT_L(2, true, true); else AT_L(2, true, false); }
+        else { if (fma) AT_L(2, false, true); else AT_L(2, false, false); }
+    } else {
+        if (linear) { if (fma) AT_L(4, true, true); else AT_L(4, true, false); }
+        else { if (fma) AT_L(4, false, true); else AT_L(4, false, false); }
+    }
 #undef AT_L
     return hipGetLastError();
 }

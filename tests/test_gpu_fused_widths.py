@@ -38,8 +38,8 @@ def limit(gpu, st):
 
 # tiles, width: one thread a tile (4, 8, 16, 32), threads of p and p - 1 points
 # (7, 10, 11, 13, 17, ...), no split (6, 9), a grid shorter than a region, one tile
-SHAPES = [(40, 4), (1, 4), (20, 6), (33, 7), (64, 8), (7, 9), (9, 10), (13, 11), (300, 13), (30, 15),
-          (25, 16), (40, 17), (11, 21), (6, 31), (9, 32), (5, 33), (11, 45), (3, 63), (8, 64), (4, 65),
+SHAPES = [(40, 4), (1, 4), (20, 6), (33, 7), (64, 8), (7, 9), (9, 10), (13, 11), (50, 12), (300, 13),
+          (30, 15), (25, 16), (40, 17), (90, 20), (11, 21), (6, 31), (9, 32), (5, 33), (11, 45), (3, 63), (8, 64), (4, 65),
           (37, 211), (1, 777), (3, 1001)]
 
 
