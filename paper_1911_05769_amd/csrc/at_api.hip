@@ -356,32 +356,52 @@ FusedShape fused_shape(const Derived &d, int s, int kind)
     return w;
 }
 
-// Estimated time per step (us) of launches of s steps on region w.  One wave
-// issues FP64 at nearly the rate of its SIMD and the oldest goes first, so a
-// launch takes as long as the SIMD with the most waves: 0.04 + 0.0205 us per point
-// of a thread for each of them and step, 5% more for ragged threads (the others
-// have powers of two), but no less than one wave's latency; and 7 us.  Measured at
-// 1024 tiles of 1024 (us per step, points per thread x waves per SIMD), order 2:
-// 16 x 2: 0.84, 8 x 3: 0.70, 20 x 1: 0.65, 10 x 2: 0.65; order 4: 8 x 3: 1.20,
-// 12 x 2: 1.12, 20 x 1: 0.96, and with more steps per launch, so that a few SIMDs
-// have two waves, 1.51.
+// Estimated time per step (us) of launches of s steps on region w.
+// A step: one wave issues FP64 at nearly the rate of its SIMD and the oldest
+// goes first, so a launch takes as long as the SIMD with the most waves: 0.035 +
+// 0.0205 us per point of a thread for each of them, 6% more for ragged threads
+// (the others have powers of two), but no less than one wave's latency; 0.01 us
+// more for a wave with a tile face.  Measured at 1024 tiles of 1024 (us per
+// step, points per thread x waves per SIMD), order 2: 16 x 2: 0.84, 8 x 3: 0.70,
+// 20 x 1: 0.65, 10 x 2: 0.65; order 4: 8 x 3: 1.20, 12 x 2: 1.12, 20 x 1: 0.96.
+// A launch: 3 us, the field's trip (1.7 us per 2^20 points, a seventh more where
+// ragged threads make it unaligned), 0.2 us for each wave of a SIMD, 1.2 us for
+// each history value a lane loads, 4 us where the field passes the stage in
+// four parts.  Without that part the estimate took 20 to 32 points for few steps
+// per launch on large grids (2^22 points, order 2, 2 steps: 24 points 10.0, 16:
+// 7.9).  Over 1214 grids and step counts of 2^14 .. 2^24 points on tiles of 16 ..
+// 4096 its choices take 1.5% more than the best kind, 3.9% without.
 double fused_cost(const Derived &d, const FusedShape &w, int s)
 {
-    const double waves = (double)((w.nblocks * w.nw + 1023) / 1024);
-    const double ragged = w.nf != w.tpt || (w.ppt & (w.ppt - 1)) != 0 ? 1.05 : 1.0;
-    const double t = std::max(0.09 + 0.0215 * w.ppt, waves * ragged * (0.04 + 0.0205 * w.ppt));
-    return t * (d.order == 4 ? 1.5 : 1.0) * (d.contracted ? 0.8 : 1.0) + 7.0 / s;
+    const double nw = (double)w.nblocks * w.nw / 1024.0, waves = std::ceil(nw);
+    const bool ragged = w.nf != w.tpt || (w.ppt & (w.ppt - 1)) != 0;
+    const double mpts = (double)d.N / (1 << 20);
+    const double hist = (double)(d.L + d.m - 1) * 2 * w.NT * d.h / (64.0 * w.nw);
+    const double step = std::max(0.09 + 0.0215 * w.ppt,
+                                 waves * (ragged ? 1.06 : 1.0) * (0.035 + 0.0205 * w.ppt));
+    const double launch = 3.0 + 0.05 * w.ppt + (ragged ? 1.95 : 1.7) * mpts + 0.2 * nw +
+                          1.2 * hist + (w.ppt >= 24 ? 4.0 : 0.0);
+    return step * (d.order == 4 ? 1.5 : 1.0) * (d.contracted ? 0.8 : 1.0) +
+           0.01 * waves * std::min(1.0, 64.0 / w.tpt) * d.h + launch / s;
+}
+
+// Grids on which variant 1 means the four-wave region (exact order: us per step
+// with 2^24 points of order 4 in tiles of 4096, 48 steps: 8.86, one wave of 16: 9.87)
+bool wide_grid(const Derived &d)
+{
+    return !d.contracted && d.N >= ((int64_t)1 << 23) && fused_shape(d, 32, kWide).ok;
 }
 
 // The kind of region of a fused launch of s steps: the one asked for where the
 // tiles take it, else (0) the one of the least estimated time; 0 when no region
-// fits this tile width.  In the exact order the largest grids run four-wave
-// regions (us per step with 2^24 points: 9.1, one wave: 9.8; with 2^22 points one
-// wave: 2.9 to 3.1).
+// fits this tile width.  Four-wave regions where a one-wave region would be rim by
+// a quarter and more (order 4, 64 steps, us per step of four waves and of the best
+// of one: 2^22 points in tiles of 4096 2.83 and 3.12, 2^24 9.10 and 9.60; 48 steps
+// 2.94 and 2.71, 8.86 and 8.81).
 int fused_kind(const Derived &d, int want, int s)
 {
     if (want != 0 && fused_shape(d, 1, want).ok) return want;
-    if (!d.contracted && d.N >= ((int64_t)1 << 23) && s >= 32 && fused_shape(d, s, kWide).ok)
+    if (!d.contracted && d.N >= ((int64_t)1 << 22) && s * d.h >= 112 && fused_shape(d, s, kWide).ok)
         return kWide;
     int pick = 0;
     for (int t = s; pick == 0 && t >= 1; t /= 2) {           // (s may be more than any region takes)
@@ -907,7 +927,7 @@ at_status at_set_variant(at_ctx *c, int32_t v)
         if (p && c->d.W % p != 0)
             return fail(AT_ERR_ARG, "variant %d needs a tile width divisible by %d", v, p);
         c->d.fppt = p ? p : fused_ppt(c->d);
-        c->kind = p == 16 && fused_kind(c->d, 0, 32) == kWide ? kWide : p;
+        c->kind = p == 16 && wide_grid(c->d) ? kWide : p;
         c->fuse = std::min(c->fuse, max_fuse(c));
     } else {
         c->fuse = at3_is_fused(v) ? 2 : 1;   // 3D: two-step variants advance two steps per launch
@@ -1348,9 +1368,11 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
             const int smax = rg.S;
             const int sadj = c->adj_fuse == 0 ? smax : (c->adj_fuse == 1 ? 0 : std::min(c->adj_fuse, smax));
             const int every = sadj > 0 ? kAdjGroup : 1;
-            int kind = fused_kind(d, every == 1 ? kRebuildKind : 0, 2);
-            if (!fused_shape(d, std::max(every, 2), kind).ok) kind = 0;
             const int64_t top = a0 + (a1 - 1 - a0) / every * every;
+            const int64_t nl = (top - a0 + kMaxFuse - 1) / kMaxFuse;           // launches
+            int kind = fused_kind(d, every == 1 ? kRebuildKind : 0,
+                                  nl > 0 ? (int)std::max<int64_t>(2, (top - a0 + nl - 1) / nl) : 2);
+            if (!fused_shape(d, std::max(every, 2), kind).ok) kind = 0;
             for (int64_t n = a0; n < top;) {
                 int s = 1;
                 if (kind) {
