@@ -214,15 +214,16 @@ at_status at_set_graph(at_ctx *ctx, int32_t use_graph);
 #define AT_DEBUG_POISON_RING 1
 at_status at_set_debug(at_ctx *ctx, int32_t flags);
 
-/* Choose the launch shape -- 1D: points per thread (the variant is 1, 2, 3 for
- * 16 or 32, 8, 4; else 0) together with steps per launch s, and the whole-grid variant 4 where the
- * grid fits one workgroup; 3D:
+/* Choose the launch shape -- 1D: the variant (0 to 3) together with steps per
+ * launch s, and the whole-grid variant 4 where the grid fits one workgroup; 3D:
  * the kernel variant (including the two-step variants) -- nothing that
  * changes results -- by timing about `trial_steps` steps (whole launches) from
  * u0 for each candidate; requires n == 0 and leaves the context at n = 0 with the ring
  * cleared.  u0 is not modified; t1 and t2 are two scratch fields.
  * Synchronises the stream.  *chosen receives s (1D; nsteps_max for variant
- * 4) or the variant (3D); at_query returns both. */
+ * 4) or the variant (3D); at_query returns both, and at_set_variant and
+ * at_set_fuse with them choose the same launches on another context of this
+ * configuration. */
 at_status at_autotune(at_ctx *ctx, const double *u0, double *t1, double *t2,
                       int32_t trial_steps, int32_t *chosen);
 
@@ -238,10 +239,11 @@ at_status at_autotune(at_ctx *ctx, const double *u0, double *t1, double *t2,
  * is positive; block widths multiples of 64 in x and of the tile rows in y).
  * Choosing 15 or 16 sets the steps per launch to 2 (a run's odd last step
  * and at_step use a one-step variant); choosing another sets it to 1, and
- * at_set_fuse(ctx, 2) selects 15 (or 16).  1D contexts: 0 automatic; 1, 2, 3 for 16, 8
+ * at_set_fuse(ctx, 2) selects 15 (or 16).  1D contexts: 0 for the points per
+ * thread of least estimated time at a run's steps per launch; 1, 2, 3 for 16, 8
  * and 4 points per thread in the fused launches (the tile width must be
- * divisible by it, AT_ERR_ARG otherwise; 1 also stands for the 32 points that
- * at_autotune may choose); 4 for the whole periodic grid in
+ * divisible by it, AT_ERR_ARG otherwise; 1 is a region of four waves instead of
+ * one on grids of 2^23 points and more in the exact order); 4 for the whole periodic grid in
  * one workgroup of 256 threads (N <= 256 x 16, with N and the tile width
  * multiples of the 4, 8 or 16 points a thread holds, AT_ERR_ARG otherwise):
  * no rim is recomputed, the neighbour exchange wraps around the workgroup,
@@ -254,6 +256,12 @@ at_status at_set_variant(at_ctx *ctx, int32_t variant);
  * (at_set_variant; chosen by at_autotune).  Any output may be NULL. */
 at_status at_query(const at_ctx *ctx, int64_t *n, int32_t *fuse_steps, int32_t *ring_levels,
                    int32_t *variant);
+
+/* What the first launch of at_run(ctx, ..., nsteps) would be (1D): the steps it
+ * advances, its points per thread and the waves of a workgroup.  Any may be
+ * NULL. */
+at_status at_launch_shape(const at_ctx *ctx, int64_t nsteps, int32_t *steps, int32_t *points,
+                          int32_t *waves);
 
 /* Copy the delay array (int8[nsteps_max][F], after the clamp) to host memory.
  * Synchronous. */

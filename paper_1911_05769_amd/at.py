@@ -92,6 +92,7 @@ SIGNATURES = {
     "at_set_graph": (ctypes.c_int, [_P, ctypes.c_int32]),
     "at_set_debug": (ctypes.c_int, [_P, ctypes.c_int32]),
     "at_query": (ctypes.c_int, [_P, _P, _P, _P, _P]),
+    "at_launch_shape": (ctypes.c_int, [_P, ctypes.c_int64, _P, _P, _P]),
     "at_delays_copy": (ctypes.c_int, [_P, _P]),
     "at_snapshot_bytes": (ctypes.c_int, [_P, _P]),
     "at_snapshot": (ctypes.c_int, [_P, _P, _P]),
@@ -327,7 +328,7 @@ class Stepper:
         _check(lib().at_set_adjoint_fuse(self._ctx, int(s)), "at_set_adjoint_fuse")
 
     def set_variant(self, v: int):
-        """Kernel variant (see at_set_variant).  1D: 0 automatic, 1/2/3 = 16/8/4
+        """Kernel variant (see at_set_variant).  1D: 0 by estimate, 1/2/3 = 16/8/4
         points per thread in fused launches, 4 = the whole grid in one
         workgroup (one launch per run; small grids only)."""
         _check(lib().at_set_variant(self._ctx, int(v)), "at_set_variant")
@@ -349,11 +350,18 @@ class Stepper:
 
     @property
     def variant(self) -> int:
-        """Kernel variant in use (1D: 0 automatic, 1/2/3 = 16/8/4 points per thread,
+        """Kernel variant in use (1D: 0 by estimate, 1/2/3 = 16/8/4 points per thread,
         4 = the whole grid in one workgroup)."""
         v = ctypes.c_int32()
         _check(lib().at_query(self._ctx, None, None, None, ctypes.byref(v)), "at_query")
         return int(v.value)
+
+    def launch_shape(self, nsteps: int):
+        """(steps, points per thread, waves per workgroup) of run()'s first launch (1D)."""
+        s, p, w = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
+        _check(lib().at_launch_shape(self._ctx, int(nsteps), ctypes.byref(s), ctypes.byref(p),
+                                     ctypes.byref(w)), "at_launch_shape")
+        return int(s.value), int(p.value), int(w.value)
 
     @property
     def n(self) -> int:

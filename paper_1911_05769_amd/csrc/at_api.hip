@@ -68,7 +68,7 @@ struct Derived {
 // Region of a workgroup of 256 threads: RL points left of the owned chunk, CH
 // owned, s*h right; where the tile width is a multiple of the points per
 // thread, RL and CH are multiples of it too.  The one-step and the general
-// kernel run these, and max_fuse_1d measures with them what at_set_fuse
+// kernel run these, and region_limit measures with them what at_set_fuse
 // accepts (a launch of the fused kernels takes as many of those steps as its
 // own region allows, launch_steps).
 struct Region1D {
@@ -76,7 +76,7 @@ struct Region1D {
     int64_t RL, CH;
 };
 
-// Points per thread that max_fuse_1d's regions are measured at: the most (16,
+// Points per thread that region_limit's regions are measured at: the most (16,
 // 8, 4) that still give every SIMD four waves of the grid and divide the tile
 // width; 16 when none divides it
 int fused_ppt(const Derived &d)
@@ -201,7 +201,7 @@ struct at_ctx {
     int fuse;
     int variant;     // 3D kernel variant (tile rows, prefetch depth, register budget)
     int32_t brick[4] = {0, 0, 0, 0};   // 3D: brick of the general kernel (0: not picked yet)
-    int kind = 0;    // 1D: region kind of the fused launches (fused_shape), 0 automatic
+    int kind = 0;    // 1D: the variant's region kind (variant_kind), 0 by the estimate
     int adj_fuse = 0;   // reverse steps per adjoint launch: 0 automatic, 1 one-step kernel
     int debug = 0;      // AT_DEBUG_* flags (at_set_debug)
     // graph replay of at_run (at_set_graph): the launch sequence of one call,
@@ -281,7 +281,7 @@ size_t edge_table_bytes(const Derived &d, int s, int NT, int ppt)
     return 8 * (std::max(stage, xch) + edges + ((size_t)s * NT * 2 + 7) / 8);
 }
 
-int max_fuse_1d(const Derived &d)
+int region_limit(const Derived &d)
 {
     int best = 1;
     for (int s = 2; s <= kMaxFuse; ++s) {
@@ -293,6 +293,15 @@ int max_fuse_1d(const Derived &d)
         best = s;
     }
     return best;
+}
+
+// (that of the variant's points per thread, and no less than variant 0's, whose
+// steps at_autotune may choose with any variant)
+int max_fuse_1d(const Derived &d)
+{
+    Derived own = d;
+    own.fppt = fused_ppt(d);
+    return std::max(region_limit(d), region_limit(own));
 }
 
 Region1D region_1d(const Derived &d, int s)
@@ -452,8 +461,9 @@ int whole_ppt(const at_ctx *c)
 // coalesced only for few points per thread
 constexpr int kRebuildKind = 4;
 
+// kind: the region asked for (fused_kind)
 at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int s, int publish,
-                    double *levels = nullptr, int every = 1, int levels_kind = 0)
+                    int kind, double *levels = nullptr, int every = 1)
 {
     const Derived &d = c->d;
     if (c->variant == kWholeVariant && !levels) {
@@ -491,8 +501,7 @@ at_status launch_1d(at_ctx *c, const double *uin, double *uout, int64_t n0, int 
     // the fused kernels' regions, except for single steps of widths that the
     // one-step kernel takes and for the few widths the regions do not fit
     const int plain = s == 1 && !levels ? step1d_plain_ppt(d.W) : 0;
-    const int want = levels ? levels_kind : c->kind;
-    const FusedShape ws = plain ? FusedShape() : fused_shape(d, s, fused_kind(d, want, s));
+    const FusedShape ws = plain ? FusedShape() : fused_shape(d, s, fused_kind(d, kind, s));
     const Region1D rg = region_1d(d, s);
     const int reg = kThreads * rg.ppt;
     Step1D a{};
@@ -574,9 +583,10 @@ int32_t (*at_ctx_brick(at_ctx *c))[4] { return &c->brick; }
 
 namespace {
 
-at_status launch_any(at_ctx *c, const double *uin, double *uout, int64_t n0, int s, int publish)
+at_status launch_any(at_ctx *c, const double *uin, double *uout, int64_t n0, int s, int publish,
+                     int kind)
 {
-    if (c->d.dim == 1) return launch_1d(c, uin, uout, n0, s, publish);
+    if (c->d.dim == 1) return launch_1d(c, uin, uout, n0, s, publish, kind);
     return at3_launch(c, uin, uout, n0, s, publish);
 }
 
@@ -625,6 +635,48 @@ hipError_t copy_ring(at_ctx *c, double *dst, const double *src, int64_t n)
         lo += count;
     }
     return e;
+}
+
+// 1D variants.  0: by the estimate (fused_kind); 1, 2, 3: 16, 8, 4 points per
+// thread in fused launches (1: the four-wave region on large grids)
+int variant_points(int v) { return v == 0 ? 0 : (v == 1 ? 16 : (v == 2 ? 8 : 4)); }
+
+int variant_kind(const Derived &d, int v)
+{
+    const int p = variant_points(v);
+    return p == 16 && wide_grid(d) ? kWide : p;
+}
+
+void select_1d(at_ctx *c, int v)
+{
+    c->d.fppt = v ? variant_points(v) : fused_ppt(c->d);
+    c->kind = variant_kind(c->d, v);
+    c->variant = v;
+}
+
+// The region kind of every launch of a 1D run of nsteps steps: the variant's, or by
+// the estimate at the steps per launch (so that variant and steps per launch name it)
+int run_kind(const at_ctx *c, int64_t nsteps)
+{
+    if (c->d.dim != 1 || c->variant == kWholeVariant) return 0;
+    int64_t s = std::max<int64_t>(1, std::min<int64_t>(c->fuse, nsteps));
+    if (c->cfg.record) {                                  // (a segment's launches are even)
+        const int64_t C = std::max<int64_t>(1, std::min<int64_t>(c->cfg.ckpt_every, nsteps));
+        const int64_t launches = (C + s - 1) / s;
+        s = (C + launches - 1) / launches;
+    }
+    return fused_kind(c->d, c->kind, (int)s);
+}
+
+// Steps of a run's next launch, `todo` before the end or the next checkpoint; home:
+// the current level is in the caller's field
+int64_t run_steps(const at_ctx *c, int kind, int64_t todo, bool home)
+{
+    if (c->d.dim != 1 || c->variant == kWholeVariant) return std::min<int64_t>(c->fuse, todo);
+    // (one more launch, 7 us, instead of a copy back at the end where that takes
+    // longer: 2^24 points 50 us)
+    return launch_steps(c->d, kind, c->fuse, todo,
+                        c->cfg.record || c->d.N < ((int64_t)1 << 21) ? -1 : (home ? 0 : 1));
 }
 
 // Debug mode AT_DEBUG_POISON_RING: after every launch, every ring slot that
@@ -922,12 +974,10 @@ at_status at_set_variant(at_ctx *c, int32_t v)
         return AT_OK;
     }
     if (c->d.dim == 1) {
-        // 0: automatic; 1, 2, 3: 16, 8, 4 points per thread in fused launches
-        const int p = v == 0 ? 0 : (v == 1 ? 16 : (v == 2 ? 8 : 4));
+        const int p = variant_points(v);
         if (p && c->d.W % p != 0)
             return fail(AT_ERR_ARG, "variant %d needs a tile width divisible by %d", v, p);
-        c->d.fppt = p ? p : fused_ppt(c->d);
-        c->kind = p == 16 && wide_grid(c->d) ? kWide : p;
+        select_1d(c, v);
         c->fuse = std::min(c->fuse, max_fuse(c));
     } else {
         c->fuse = at3_is_fused(v) ? 2 : 1;   // 3D: two-step variants advance two steps per launch
@@ -946,6 +996,25 @@ at_status at_query(const at_ctx *c, int64_t *n, int32_t *fuse, int32_t *R, int32
     return AT_OK;
 }
 
+at_status at_launch_shape(const at_ctx *c, int64_t nsteps, int32_t *steps, int32_t *points,
+                          int32_t *waves)
+{
+    if (!c) return fail(AT_ERR_ARG, "null context");
+    if (c->d.dim != 1) return fail(AT_ERR_ARG, "the launch shape is a 1D context's");
+    if (nsteps < 1) return fail(AT_ERR_ARG, "nsteps < 1");
+    const int64_t C = c->cfg.ckpt_every;
+    const int64_t todo = c->cfg.record ? std::min<int64_t>(nsteps, C - c->n % C) : nsteps;
+    const int kind = run_kind(c, nsteps);
+    const int s = (int)run_steps(c, kind, todo, true);
+    const int plain = s == 1 ? step1d_plain_ppt(c->d.W) : 0;
+    const FusedShape w = plain ? FusedShape() : fused_shape(c->d, s, fused_kind(c->d, kind, s));
+    const bool whole = c->variant == kWholeVariant;
+    if (steps) *steps = s;
+    if (points) *points = whole ? whole_ppt(c) : (w.ok ? w.ppt : (plain ? plain : step1d_points_per_thread()));
+    if (waves) *waves = !whole && w.ok ? w.nw : kThreads / 64;
+    return AT_OK;
+}
+
 at_status at_step(at_ctx *c, const double *u_in, double *u_out)
 {
     if (!c || !u_in || !u_out) return fail(AT_ERR_ARG, "null argument");
@@ -958,7 +1027,7 @@ at_status at_step(at_ctx *c, const double *u_in, double *u_out)
         const at_status sp = at3_publish(c, u_in, c->n);
         if (sp) return sp;
     }
-    at_status st = launch_any(c, u_in, u_out, c->n, 1, 1);
+    at_status st = launch_any(c, u_in, u_out, c->n, 1, 1, c->kind);
     if (st) return st;
     c->n += 1;
     AT_HIP(poison_ring(c, c->n));
@@ -974,6 +1043,7 @@ at_status run_launches(at_ctx *c, double *u, double *scratch, int64_t nsteps)
     double *cur = u, *oth = scratch;
     int64_t left = nsteps;
     const int64_t C = c->cfg.ckpt_every;
+    const int kind = run_kind(c, nsteps);
     if (c->d.dim == 3 && nsteps > 0) {        // the face values of level n, from u
         const at_status sp = at3_publish(c, u, c->n);
         if (sp) return sp;
@@ -985,16 +1055,11 @@ at_status run_launches(at_ctx *c, double *u, double *scratch, int64_t nsteps)
                 AT_HIP(launch_copy(c->ckpt + (c->n / C) * c->d.N, cur, c->d.N, c->st));
             todo = std::min<int64_t>(todo, C - c->n % C);
         }
-        int64_t s = std::min<int64_t>(c->fuse, todo);
-        // (one more launch, 7 us, instead of a copy back at the end where that
-        // takes longer: 2^24 points 50 us)
-        if (c->d.dim == 1 && c->variant != kWholeVariant)
-            s = launch_steps(c->d, c->kind, c->fuse, todo,
-                             c->cfg.record || c->d.N < ((int64_t)1 << 21) ? -1 : (cur == u ? 0 : 1));
+        const int64_t s = run_steps(c, kind, todo, cur == u);
         // 1D without the edge tape: only the last L + m - 1 levels of a launch
         // reach the ring (the next launch reads no older level)
         at_status st = launch_any(c, cur, oth, c->n, (int)s,
-                                  (c->d.dim == 1 && !c->cfg.record) ? 2 : 1);
+                                  (c->d.dim == 1 && !c->cfg.record) ? 2 : 1, kind);
         if (st) return st;
         std::swap(cur, oth);
         c->n += s;
@@ -1017,7 +1082,8 @@ at_status at_run(at_ctx *c, double *u, double *scratch, int64_t nsteps)
                     (long long)(c->n + nsteps), (long long)c->cfg.nsteps_max);
     if (!c->use_graph || nsteps == 0) return run_launches(c, u, scratch, nsteps);
     // graph replay: the cached graph applies when it was captured for the same
-    // start step, length, fields and launch choices
+    // start step, length, fields and launch choices (a 1D region kind follows from
+    // variant, steps per launch and length)
     if (!(c->gexec && c->g_n0 == c->n && c->g_nsteps == nsteps && c->g_u == u &&
           c->g_s == scratch && c->g_fuse == c->fuse && c->g_variant == c->variant &&
           c->g_debug == c->debug)) {
@@ -1163,35 +1229,46 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
     if (c->cfg.record) return fail(AT_ERR_STATE, "autotune is not available in record mode");
     if (trial_steps < 1 || trial_steps > c->cfg.nsteps_max)
         return fail(AT_ERR_ARG, "trial_steps must be in 1..nsteps_max");
-    // 1D: (points per thread, steps per launch) pairs; 3D: the kernel variant
-    // (one or two steps per launch)
-    std::vector<std::pair<int, int>> cands;       // (points per thread or variant, steps)
+    // (variant, steps per launch) pairs as at_set_variant and at_set_fuse take them
+    std::vector<std::pair<int, int>> cands;
     if (c->d.dim == 1) {
-        const int mf = max_fuse(c);
-        if (c->d.N >= ((int64_t)1 << 23))
-            for (int s : {48, 64, 40, 32})
-                if (s <= mf && fused_shape(c->d, s, kWide).ok) cands.push_back({kWide, s});
-        // of each kind the most steps for each number of waves per SIMD, and a
-        // few round counts; of those the twelve of the least estimates
+        // of each region kind that a variant names (0: the estimate's at that many
+        // steps) the most steps for each number of waves per SIMD, and a few round
+        // counts; of those the twelve of the least estimates
         std::vector<std::pair<double, std::pair<int, int>>> est;
-        for (int p : kFusedKinds) {
+        for (int v : {1, 2, 3, 0}) {
+            Derived d = c->d;
+            if (v && d.W % variant_points(v) != 0) continue;
+            d.fppt = v ? variant_points(v) : fused_ppt(d);
+            const int mf = max_fuse_1d(d);
             int64_t waves = 0;
+            int last = 0;
             for (int s = std::min(mf, kMaxFuse); s >= 2; --s) {
-                const FusedShape w = fused_shape(c->d, s, p);
-                if (!w.ok) continue;
-                const int64_t now = (w.nblocks + 1023) / 1024;
-                if (now == waves && s % 16 != 0 && (s > 16 || s % 4 != 0)) continue;
+                const int kind = v ? variant_kind(d, v) : fused_kind(d, 0, s);
+                bool named = false;                      // by one of the variants above
+                for (int w = 1; w <= 3; ++w)
+                    named = named || (v == 0 && d.W % variant_points(w) == 0 && variant_kind(d, w) == kind);
+                const FusedShape w = fused_shape(d, s, kind);
+                if (!w.ok || named) continue;
+                const int64_t now = (w.nblocks * w.nw + 1023) / 1024;
+                if (kind == last && now == waves && s % 16 != 0 && (s > 16 || s % 4 != 0)) continue;
                 waves = now;
-                est.push_back({fused_cost(c->d, w, s), {p, s}});
+                last = kind;
+                // (always tried on the large grids)
+                if (kind == kWide && v == 1 && (s == 32 || s == 40 || s == 48 || s == 64))
+                    cands.push_back({v, s});
+                else if (kind != kWide) est.push_back({fused_cost(d, w, s), {v, s}});
             }
         }
         std::sort(est.begin(), est.end());
         for (size_t i = 0; i < est.size() && i < 12; ++i) cands.push_back(est[i].second);
-        if (cands.empty())                                    // widths without such regions
+        if (cands.empty()) {                                  // widths without such regions
+            const int mf = max_fuse(c);
             for (int s : {64, 32, 16, 8, 4})
                 if (s <= mf) cands.push_back({0, s});
-        if (est.empty()) cands.push_back({0, 1});
-        if (whole_ppt(c) != 0) cands.push_back({-kWholeVariant, 0});   // one launch per run
+            cands.push_back({0, 1});
+        }
+        if (whole_ppt(c) != 0) cands.push_back({kWholeVariant, 0});   // one launch per run
     } else {
         for (int v = 0; v < at3_variants(); ++v)
             if (at3_variant_ok(&c->cfg, v) && (at3_is_aligned(v) || at3_is_fused(v) || cands.empty() || v == 9))
@@ -1207,22 +1284,15 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
     const int keep_graph = c->use_graph;
     c->use_graph = 0;                         // time the launches themselves
     at_status st = AT_OK;
-    // select a candidate: the variant (1D: points per thread) and steps per launch
+    // select a candidate
     auto choose = [&](std::pair<int, int> vs) {
-        if (c->d.dim == 1 && vs.first == -kWholeVariant) {
-            c->variant = kWholeVariant;
-            c->fuse = (int)std::min<int64_t>(c->cfg.nsteps_max, INT32_MAX);
-            return;
-        }
         c->variant = vs.first;
         c->fuse = vs.second;
-        if (c->d.dim == 1) {
-            // the variant at_set_variant would take for this many points per
-            // thread (32 is variant 1 too), 0 (by the estimate) where it takes none
-            const int p = std::abs(vs.first);
-            const int v = p == 16 || p == 32 ? 1 : (p == 8 ? 2 : (p == 4 ? 3 : 0));
-            c->kind = vs.first;
-            c->variant = v && c->d.W % std::min(p, 16) == 0 ? v : 0;
+        if (c->d.dim != 1) return;
+        select_1d(c, vs.first == kWholeVariant ? 0 : vs.first);
+        if (vs.first == kWholeVariant) {
+            c->variant = kWholeVariant;
+            c->fuse = (int)std::min<int64_t>(c->cfg.nsteps_max, INT32_MAX);
         }
     };
     // twice over all candidates, not twice each: an idle device's clock takes some
@@ -1380,7 +1450,7 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
                     s = s < every ? every : s / every * every;
                 }
                 at_status st = launch_1d(c, c->seg + (n - a0) * N, c->seg + (n + s - a0) * N, n, s,
-                                         0, s > 1 ? c->seg + (n - a0) * N : nullptr, every, kind);
+                                         0, kind, s > 1 ? c->seg + (n - a0) * N : nullptr, every);
                 if (st) return st;
                 n += s;
             }
@@ -1667,7 +1737,7 @@ static at_status batch_layout(const at_config *cfgs, int32_t count, std::vector<
         if (ds[j].W % step1d_points_per_thread() != 0)
             return fail(AT_ERR_SHAPE, "instance %d: tile width %lld is not a multiple of %d", j,
                         (long long)ds[j].W, step1d_points_per_thread());
-        smax = std::min(smax, max_fuse_1d(ds[j]));
+        smax = std::min(smax, region_limit(ds[j]));
     }
     // steps-per-launch limit for each points-per-thread choice (16 gives the
     // largest regions, so the rings sized for it serve every choice)
@@ -1677,7 +1747,7 @@ static at_status batch_layout(const at_config *cfgs, int32_t count, std::vector<
         for (int j = 0; j < count; ++j) {
             Derived d = ds[j];
             d.fppt = ppts[i];
-            mf_ppt[i] = std::min(mf_ppt[i], max_fuse_1d(d));
+            mf_ppt[i] = std::min(mf_ppt[i], region_limit(d));
         }
         mf_ppt[i] = std::min(mf_ppt[i], smax);
     }
