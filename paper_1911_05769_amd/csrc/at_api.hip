@@ -380,7 +380,10 @@ FusedShape fused_shape(const Derived &d, int s, int kind)
 // per launch on large grids (2^22 points, order 2, 2 steps: 24 points 10.0, 16:
 // 7.9).  Over 1214 grids and step counts of 2^14 .. 2^24 points on tiles of 16 ..
 // 4096 its choices take 1.5% more than the best kind, 3.9% without.
-double fused_cost(const Derived &d, const FusedShape &w, int s)
+// stores: launches that write every fourth level from registers, coalesced only for
+// few points per thread (2^20 points, order 2, us per step of a whole adjoint: 8
+// points 3.66, 10 3.70, 20 3.84; order 4: 12 6.48, 20 6.59).
+double fused_cost(const Derived &d, const FusedShape &w, int s, bool stores)
 {
     const double nw = (double)w.nblocks * w.nw / 1024.0, waves = std::ceil(nw);
     const bool ragged = w.nf != w.tpt || (w.ppt & (w.ppt - 1)) != 0;
@@ -391,7 +394,8 @@ double fused_cost(const Derived &d, const FusedShape &w, int s)
     const double launch = 3.0 + 0.05 * w.ppt + (ragged ? 1.95 : 1.7) * mpts + 0.2 * nw +
                           1.2 * hist + (w.ppt >= 24 ? 4.0 : 0.0);
     return step * (d.order == 4 ? 1.5 : 1.0) * (d.contracted ? 0.8 : 1.0) +
-           0.01 * waves * std::min(1.0, 64.0 / w.tpt) * d.h + launch / s;
+           0.01 * waves * std::min(1.0, 64.0 / w.tpt) * d.h + launch / s +
+           (stores ? (ragged ? 0.03 : 0.02) * w.ppt * mpts : 0.0);
 }
 
 // Grids on which variant 1 means the four-wave region (exact order: us per step
@@ -407,10 +411,11 @@ bool wide_grid(const Derived &d)
 // a quarter and more (order 4, 64 steps, us per step of four waves and of the best
 // of one: 2^22 points in tiles of 4096 2.83 and 3.12, 2^24 9.10 and 9.60; 48 steps
 // 2.94 and 2.71, 8.86 and 8.81).
-int fused_kind(const Derived &d, int want, int s)
+int fused_kind(const Derived &d, int want, int s, bool stores = false)
 {
     if (want != 0 && fused_shape(d, 1, want).ok) return want;
-    if (!d.contracted && d.N >= ((int64_t)1 << 22) && s * d.h >= 112 && fused_shape(d, s, kWide).ok)
+    if (!d.contracted && !stores && d.N >= ((int64_t)1 << 22) && s * d.h >= 112 &&
+        fused_shape(d, s, kWide).ok)
         return kWide;
     int pick = 0;
     for (int t = s; pick == 0 && t >= 1; t /= 2) {           // (s may be more than any region takes)
@@ -418,7 +423,7 @@ int fused_kind(const Derived &d, int want, int s)
         for (int p : kFusedKinds) {
             const FusedShape w = fused_shape(d, t, p);
             if (!w.ok) continue;
-            const double cost = fused_cost(d, w, t);
+            const double cost = fused_cost(d, w, t, stores);
             if (pick == 0 || cost < least) { pick = p; least = cost; }
         }
     }
@@ -1257,7 +1262,7 @@ at_status at_autotune(at_ctx *c, const double *u0, double *t1, double *t2, int32
                 // (always tried on the large grids)
                 if (kind == kWide && v == 1 && (s == 32 || s == 40 || s == 48 || s == 64))
                     cands.push_back({v, s});
-                else if (kind != kWide) est.push_back({fused_cost(d, w, s), {v, s}});
+                else if (kind != kWide) est.push_back({fused_cost(d, w, s, false), {v, s}});
             }
         }
         std::sort(est.begin(), est.end());
@@ -1441,7 +1446,8 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
             const int64_t top = a0 + (a1 - 1 - a0) / every * every;
             const int64_t nl = (top - a0 + kMaxFuse - 1) / kMaxFuse;           // launches
             int kind = fused_kind(d, every == 1 ? kRebuildKind : 0,
-                                  nl > 0 ? (int)std::max<int64_t>(2, (top - a0 + nl - 1) / nl) : 2);
+                                  nl > 0 ? (int)std::max<int64_t>(2, (top - a0 + nl - 1) / nl) : 2,
+                                  true);
             if (!fused_shape(d, std::max(every, 2), kind).ok) kind = 0;
             for (int64_t n = a0; n < top;) {
                 int s = 1;
