@@ -345,16 +345,22 @@ at_status at_batch_reset(at_batch *b);
 at_status at_batch_query(const at_batch *b, int64_t *n, int32_t *fuse_steps, int32_t *max_fuse,
                          int32_t *variant);
 
-/* Points per thread of the batched kernel: 0 (default) and 1: 16 (or what
- * at_batch_autotune chose), 2: 8, 3: 4; fewer where a tile would be a single
- * thread.  Fewer points per thread make shorter regions (more workgroups, more
+/* What the first launch of at_batch_run(b, ..., nsteps) would be: the steps it
+ * advances and its points per thread.  Either may be NULL. */
+at_status at_batch_launch_shape(const at_batch *b, int64_t nsteps, int32_t *steps,
+                                int32_t *points);
+
+/* Points per thread of the batched kernel: 0 (default) and 1: 16, or 32 where an
+ * estimate of the time at the steps per launch has it (large batches, long
+ * launches), 2: 8, 3: 4; fewer where a tile would be a single thread.  Fewer points per thread make shorter regions (more workgroups, more
  * redundant rim work per point).  Steps per launch are lowered to the limit
  * of the new layout if needed.  Every choice gives the same bits. */
 at_status at_batch_set_variant(at_batch *b, int32_t variant);
 
 /* Choose the batch's points per thread and steps per launch by timing (same
  * contract as at_autotune, per batch); *chosen receives the steps per
- * launch, at_batch_query both.  Steps per launch are tried largest first, and
+ * launch, at_batch_query both, and at_batch_set_variant and at_batch_set_fuse
+ * with them choose the same launches on another batch of these instances.  Steps per launch are tried largest first, and
  * a smaller count replaces a larger one only when it is 2% faster; a trial runs
  * about trial_steps steps, in whole launches. */
 at_status at_batch_autotune(at_batch *b, double *const *u_dev, double *const *t1,

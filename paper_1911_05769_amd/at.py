@@ -109,6 +109,7 @@ SIGNATURES = {
     "at_batch_set_fuse": (ctypes.c_int, [_P, ctypes.c_int32]),
     "at_batch_reset": (ctypes.c_int, [_P]),
     "at_batch_query": (ctypes.c_int, [_P, _P, _P, _P, _P]),
+    "at_batch_launch_shape": (ctypes.c_int, [_P, ctypes.c_int64, _P, _P]),
     "at_batch_set_variant": (ctypes.c_int, [_P, ctypes.c_int32]),
 }
 
@@ -495,9 +496,16 @@ class Batch:
                                     None), "at_batch_query")
         return int(n.value), int(s.value), int(m.value)
 
+    def launch_shape(self, nsteps: int):
+        """(steps, points per thread) of run()'s first launch."""
+        s, p = ctypes.c_int32(), ctypes.c_int32()
+        _check(lib().at_batch_launch_shape(self._h, int(nsteps), ctypes.byref(s), ctypes.byref(p)),
+               "at_batch_launch_shape")
+        return int(s.value), int(p.value)
+
     @property
     def variant(self) -> int:
-        """Points-per-thread variant (0/1: 16, 2: 8, 3: 4)."""
+        """Points-per-thread variant (0/1: 16 or 32, 2: 8, 3: 4)."""
         v = ctypes.c_int32()
         _check(lib().at_batch_query(self._h, None, None, None, ctypes.byref(v)),
                "at_batch_query")

@@ -1560,8 +1560,8 @@ struct at_batch {
     int64_t ring_all_doubles = 0;
     int64_t nsteps_max = 0;   // smallest over the instances
     int max_fuse = 1, fuse = 1;
-    int kind = 16;            // region kind asked for (fused_shape)
-    int variant = 0;          // 0 automatic (16), 1, 2, 3: 16, 8, 4 points per thread
+    int variant = 0;          // 0 and 1: 16 points per thread or 32 (batch_plan), 2: 8, 3: 4
+    int plan_for = 0, kind = 16, steps = 1;   // batch_plan's answer for runs of plan_for steps and more
     int mf_ppt[3] = {1, 1, 1};   // steps-per-launch limit for 16, 8, 4 points per thread
     int64_t n = 0;
     // device tables (two slots: the run's s and its tail)
@@ -1580,7 +1580,7 @@ struct at_batch {
     bool has_graph = false;
     hipGraphExec_t gexec = nullptr;
     int64_t g_n0 = -1, g_nsteps = -1;
-    int g_fuse = 0, g_kind = 0;
+    int g_fuse = 0, g_variant = -1;
     uint64_t g_key = 0;
 };
 
@@ -1603,27 +1603,46 @@ void drop_graph(at_batch *b)
     b->gexec = nullptr;
 }
 
-// The region kind every instance's tiles take: the one asked for, or fewer
-// points per thread (4 always fits: the tile widths are multiples of 16)
-int batch_kind(const at_batch *b)
+// Whether launches of s steps take 32 points per thread instead of 16: half as many
+// waves of 1.9 times the time a step, but rims half as large a part of a region, so
+// where the batch fills the SIMDs many times over.  By the waves of the busiest SIMD
+// and their time per step (fused_cost), and for 32 points what a wave whose lanes
+// are tile faces takes longer.  Measured (us per step, 16 and 32 points): tiles of
+// 256, order 4, 2^24 points: 16 steps 11.3 and 11.3, 32: 11.2 and 10.2, 48: 11.5 and
+// 9.9; 2^22 points, 48: 3.07 and 3.41; tiles of 64, 2^24 points, 16: 14.7 and 17.5.
+bool batch_takes_32(const at_batch *b, int s)
 {
-    if (b->kind < 0) return b->kind;                  // the tuner's, which fits
-    for (int p = b->kind; p > 4; p /= 2) {
-        bool ok = true;
-        for (const Derived &d : b->d) ok = ok && d.W % p == 0 && fused_shape(d, 1, p).ok;
-        if (ok) return p;
+    double nb16 = 0.0, nb32 = 0.0, faces = 0.0;
+    for (const Derived &d : b->d) {
+        const FusedShape x = fused_shape(d, s, 16), y = fused_shape(d, s, 32);
+        if (d.W % 32 != 0 || !x.ok || !y.ok) return false;
+        nb16 += (double)x.nblocks;
+        nb32 += (double)y.nblocks;
+        faces += (double)y.nblocks * (1.03 + 6.0 * d.h / (double)d.W);
     }
-    return 4;
+    return std::ceil(nb32 / 1024.0) * (0.035 + 0.0205 * 32) * (faces / nb32) <
+           std::ceil(nb16 / 1024.0) * (0.035 + 0.0205 * 16);
 }
 
-// Steps per launch: the number set, as far as every instance's regions allow
-int batch_fuse(const at_batch *b)
+// Region kind and steps per launch of runs of nsteps steps: the variant's points per
+// thread, or fewer where an instance's tiles do not take them (4 always fits: the
+// tile widths are multiples of 16), and the number of steps set, as far as every
+// instance's regions allow
+void batch_plan(at_batch *b, int64_t nsteps)
 {
-    const int kind = batch_kind(b);
-    int s = b->fuse;
+    const int s = (int)std::min<int64_t>(b->fuse, nsteps);
+    if (b->plan_for == s) return;
+    b->plan_for = s;
+    b->kind = 4;
+    for (int p = b->variant <= 1 ? 16 : variant_points(b->variant); p > 4; p /= 2) {
+        bool ok = true;
+        for (const Derived &d : b->d) ok = ok && d.W % p == 0 && fused_shape(d, 1, p).ok;
+        if (ok) { b->kind = p; break; }
+    }
+    if (b->kind == 16 && batch_takes_32(b, s)) b->kind = 32;
+    b->steps = s;
     for (const Derived &d : b->d)
-        while (s > 1 && !fused_shape(d, s, kind).ok) --s;
-    return s;
+        while (b->steps > 1 && !fused_shape(d, b->steps, b->kind).ok) --b->steps;
 }
 
 at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *const *scr,
@@ -1633,7 +1652,6 @@ at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *c
                         ((uint64_t)b->kind * 0xD1B54A32D192ED03ULL);
     if (b->slot_s[slot] == s && b->slot_key[slot] == k2) return AT_OK;
     drop_graph(b);    // a cached graph reads these tables
-    const int kind = batch_kind(b);
     std::vector<Step1D> &D = b->hdesc[slot];
     std::vector<int2> &T = b->htbl[slot];
     D.resize(b->count);
@@ -1641,7 +1659,7 @@ at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *c
     size_t lds = 0;
     for (int j = 0; j < b->count; ++j) {
         const Derived &d = b->d[j];
-        const FusedShape ws = fused_shape(d, s, kind);
+        const FusedShape ws = fused_shape(d, s, b->kind);
         if (!ws.ok) return fail(AT_ERR_STATE, "batch: no region for %d steps per launch", s);
         Step1D &a = D[j];
         a.uin = u[j];
@@ -1696,16 +1714,14 @@ at_status batch_launches(at_batch *b, int64_t n0, int64_t nsteps, double *const 
 {
     int flip = 0;
     int64_t done = 0;
-    const int f = batch_fuse(b), kind = batch_kind(b);
     // launches of even length (two lengths at most), an even number of them: a copy
     // back of every instance's field costs more than one (256 of them: 0.6 ms)
     while (done < nsteps) {
-        const int64_t left = nsteps - done, n = launch_count(left, f, flip);
+        const int64_t left = nsteps - done, n = launch_count(left, b->steps, flip);
         const int s = (int)((left + n - 1) / n);
         const int slot = s == b->slot_s[0] ? 0 : 1;
         AT_HIP(launch_wave1d_batch(b->desc_dev[slot], b->tbl_dev[slot], b->slot_blocks[slot],
-                                   b->order, b->linear, b->fma, std::abs(kind), kind < 0 ? 4 : 1,
-                                   n0 + done, flip,
+                                   b->order, b->linear, b->fma, b->kind, n0 + done, flip,
                                    b->slot_lds[slot], stream));
         flip ^= 1;
         done += s;
@@ -1764,7 +1780,7 @@ static at_status batch_layout(const at_config *cfgs, int32_t count, std::vector<
         off_delays[j] = off;
         off = align_up(off + (uint64_t)cfgs[j].nsteps_max * (uint64_t)ds[j].F);
         int64_t most = 0;
-        for (int p : {kWide, 32, 16, 8, 4})
+        for (int p : {32, 16, 8, 4})
             for (int s = 1; s <= smax; ++s) most = std::max(most, fused_shape(ds[j], s, p).nblocks);
         tbl_cap += most;
     }
@@ -1838,7 +1854,6 @@ at_status at_batch_init(const at_config *cfgs, int32_t count, void *workspace,
     b->d = ds;
     b->R = Rs;
     for (int i = 0; i < 3; ++i) b->mf_ppt[i] = mfp[i];
-    b->kind = 16;
     b->max_fuse = mfp[0];
     b->fuse = cfgs[0].fuse_steps > 0 ? std::min<int>(cfgs[0].fuse_steps, b->max_fuse) : 1;
     b->nsteps_max = cfgs[0].nsteps_max;
@@ -1888,6 +1903,7 @@ at_status at_batch_set_fuse(at_batch *b, int32_t s)
     if (s < 1 || s > b->max_fuse)
         return fail(AT_ERR_ARG, "fuse_steps must be in 1..%d for this batch", b->max_fuse);
     b->fuse = s;
+    b->plan_for = 0;
     return AT_OK;
 }
 
@@ -1897,7 +1913,7 @@ at_status at_batch_set_variant(at_batch *b, int32_t v)
     if (v < 0 || v > 3) return fail(AT_ERR_ARG, "batch variant must be in 0..3");
     const int idx = v <= 1 ? 0 : v - 1;               // 16, 8, 4 points per thread
     b->variant = v;
-    b->kind = idx == 0 ? 16 : (idx == 1 ? 8 : 4);
+    b->plan_for = 0;
     b->max_fuse = b->mf_ppt[idx];
     b->fuse = std::min(b->fuse, b->max_fuse);
     b->slot_s[0] = b->slot_s[1] = 0;                  // tables are rebuilt for the new layout
@@ -1926,13 +1942,14 @@ at_status at_batch_run(at_batch *b, double *const *u, double *const *scr, int64_
     if (nsteps == 0) return AT_OK;
     const uint64_t key = ptr_key(u, scr, b->count);
     if (use_graph && b->has_graph && b->g_n0 == b->n && b->g_nsteps == nsteps &&
-        b->g_fuse == b->fuse && b->g_kind == b->kind && b->g_key == key) {
+        b->g_fuse == b->fuse && b->g_variant == b->variant && b->g_key == key) {
         AT_HIP(hipGraphLaunch(b->gexec, b->st));
         b->n += nsteps;
         return AT_OK;
     }
     // the run's launches are s or s - 1 steps long (batch_launches)
-    const int64_t nl = launch_count(nsteps, batch_fuse(b), 0);
+    batch_plan(b, nsteps);
+    const int64_t nl = launch_count(nsteps, b->steps, 0);
     const int s_long = (int)((nsteps + nl - 1) / nl);
     at_status st = batch_tables(b, 0, s_long, u, scr, key);
     if (st) return st;
@@ -1961,7 +1978,7 @@ at_status at_batch_run(at_batch *b, double *const *u, double *const *scr, int64_
     b->g_n0 = b->n;
     b->g_nsteps = nsteps;
     b->g_fuse = b->fuse;
-    b->g_kind = b->kind;
+    b->g_variant = b->variant;
     b->g_key = key;
     AT_HIP(hipGraphLaunch(b->gexec, b->st));
     b->n += nsteps;
@@ -1982,22 +1999,22 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
         (void)hipEventDestroy(e0);
         return fail(AT_ERR_HIP, "at_batch_autotune: hipEventCreate failed");
     }
-    // points per thread (32 and 16: variant 1; 8: 2; 4: 3) and steps per launch,
-    // the largest steps per launch first
-    struct Trial { int kind, variant, s; float ms; };
+    // variant and steps per launch, the largest steps per launch first
+    struct Trial { int variant, s; float ms; };
     std::vector<Trial> tr;
     at_status st = AT_OK;
-    for (int k : {kWide, 32, 16, 8, 4}) {
-        const int v = std::abs(k) >= 16 ? 1 : (k == 8 ? 2 : 3);
-        if (st == AT_OK) st = at_batch_set_variant(b, v);
+    for (int v = 1; v <= 3 && st == AT_OK; ++v) {
+        st = at_batch_set_variant(b, v);
+        const int p = variant_points(v);
         bool ok = st == AT_OK;
-        for (const Derived &d : b->d) ok = ok && d.W % std::abs(k) == 0 && fused_shape(d, 1, k).ok;
+        for (const Derived &d : b->d) ok = ok && d.W % p == 0 && fused_shape(d, 1, p).ok;
         if (!ok) continue;
-        b->kind = k;
         for (int ci = (int)(sizeof(cands) / sizeof(cands[0])) - 1; ci >= 0; --ci) {
+            if (cands[ci] > b->max_fuse) continue;
             b->fuse = cands[ci];
-            if (cands[ci] <= b->max_fuse && batch_fuse(b) == cands[ci])
-                tr.push_back({k, v, cands[ci], 1e30f});
+            b->plan_for = 0;
+            batch_plan(b, b->fuse);
+            if (b->steps == b->fuse) tr.push_back({v, b->fuse, 1e30f});
         }
     }
     // every candidate twice in turn (the first run builds its tables), then those
@@ -2010,7 +2027,6 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
             Trial &t = tr[i];
             if (round > 0 && t.ms > near) continue;
             st = at_batch_set_variant(b, t.variant);
-            b->kind = t.kind;
             const int steps = trial_length(trial_steps, t.s, b->nsteps_max);
             for (int rep = 0; rep < 2 && st == AT_OK; ++rep) {
                 st = at_batch_reset(b);
@@ -2018,6 +2034,7 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
                 for (int j = 0; j < b->count && st == AT_OK && e == hipSuccess; ++j)
                     e = launch_copy(t1[j], u0[j], b->d[j].N, b->st);
                 b->fuse = t.s;
+                b->plan_for = 0;
                 if (st == AT_OK && e == hipSuccess) e = hipEventRecord(e0, b->st);
                 if (st == AT_OK && e == hipSuccess) st = at_batch_run(b, t1, t2, steps, 0);
                 if (st == AT_OK && e == hipSuccess) e = hipEventRecord(e1, b->st);
@@ -2041,12 +2058,23 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
     const int best_s = tr.empty() ? 1 : tr[best].s;
     st = at_batch_set_variant(b, tr.empty() ? 1 : tr[best].variant);
     if (st) return st;
-    if (!tr.empty()) b->kind = tr[best].kind;
     st = at_batch_reset(b);
     if (st) return st;
     AT_HIP(hipStreamSynchronize(b->st));
     b->fuse = best_s;
+    b->plan_for = 0;
     if (chosen) *chosen = best_s;
+    return AT_OK;
+}
+
+at_status at_batch_launch_shape(const at_batch *b, int64_t nsteps, int32_t *steps, int32_t *points)
+{
+    if (!b) return fail(AT_ERR_ARG, "null batch");
+    if (nsteps < 1) return fail(AT_ERR_ARG, "nsteps < 1");
+    batch_plan(const_cast<at_batch *>(b), nsteps);    // (what the next run computes anyway)
+    const int64_t nl = launch_count(nsteps, b->steps, 0);
+    if (steps) *steps = (int32_t)((nsteps + nl - 1) / nl);
+    if (points) *points = b->kind;
     return AT_OK;
 }
 

@@ -137,7 +137,7 @@ size_t wave1d_lds_bytes(int order, int s, int NT, int D, int ppt, int nw);
 hipError_t launch_wave1d(const Step1D &a, int order, bool linear, bool fma, int ppt, int nw,
                          int64_t nblocks, hipStream_t st);
 hipError_t launch_wave1d_batch(const Step1D *descs, const int2 *tbl, int64_t nblocks, int order,
-                               bool linear, bool fma, int ppt, int nw, int64_t n0, int flip, size_t lds,
+                               bool linear, bool fma, int ppt, int64_t n0, int flip, size_t lds,
                                hipStream_t st);
 hipError_t launch_adj1d(const Adj1D &a, int order, bool linear, int64_t nblocks,
                         hipStream_t st);

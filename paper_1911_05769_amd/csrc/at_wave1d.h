@@ -466,8 +466,8 @@ void k_wave1d(Step1D a)
 // Batched form: workgroup b advances chunk tbl[b].y of instance tbl[b].x;
 // instance descriptors carry each instance's grid, ring, delays and
 // coefficients; flip = 1 swaps the field pointers (ping-pong launches).
-template <int ORDER, bool LINEAR, bool FMA, int PPT, int NW>
-__global__ __launch_bounds__(kWave * NW)
+template <int ORDER, bool LINEAR, bool FMA, int PPT>
+__global__ __launch_bounds__(kWave)
 __attribute__((amdgpu_waves_per_eu(wave_occupancy(PPT))))
 void k_wave1d_batch(const Step1D *descs, const int2 *tbl, int64_t n0, int flip)
 {
@@ -480,7 +480,7 @@ void k_wave1d_batch(const Step1D *descs, const int2 *tbl, int64_t n0, int flip)
         a.uin = a.uout;
         a.uout = const_cast<double *>(t);
     }
-    wave1d_body<ORDER, LINEAR, FMA, PPT, false, NW>(a, e.y);
+    wave1d_body<ORDER, LINEAR, FMA, PPT, false, 1>(a, e.y);
 }
 
 template <int ORDER>
@@ -516,19 +516,17 @@ hipError_t launch_wave1d_order(const Step1D &a, bool linear, bool fma, int ppt, 
 
 template <int ORDER>
 hipError_t launch_wave1d_batch_order(const Step1D *descs, const int2 *tbl, int64_t nblocks,
-                                     bool linear, bool fma, int ppt, int nw, int64_t n0, int flip,
+                                     bool linear, bool fma, int ppt, int64_t n0, int flip,
                                      size_t lds, hipStream_t st)
 {
-    const dim3 grid((unsigned)nblocks), block(kWave * nw);
-#define AT_WB(LI, F, P, NW) hipLaunchKernelGGL((k_wave1d_batch<ORDER, LI, F, P, NW>), grid, block, lds, st, descs, tbl, n0, flip)
+    const dim3 grid((unsigned)nblocks), block(kWave);
+#define AT_WB(LI, F, P) hipLaunchKernelGGL((k_wave1d_batch<ORDER, LI, F, P>), grid, block, lds, st, descs, tbl, n0, flip)
 #define AT_WBP(LI, F)                                                                    \
     do {                                                                                 \
-        if (nw == 4 && ppt == 16) AT_WB(LI, F, 16, 4);                                   \
-        else if (nw != 1) return hipErrorInvalidValue;                                   \
-        else if (ppt == 32) AT_WB(LI, F, 32, 1);                                         \
-        else if (ppt == 16) AT_WB(LI, F, 16, 1);                                         \
-        else if (ppt == 8) AT_WB(LI, F, 8, 1);                                           \
-        else if (ppt == 4) AT_WB(LI, F, 4, 1);                                           \
+        if (ppt == 32) AT_WB(LI, F, 32);                                                 \
+        else if (ppt == 16) AT_WB(LI, F, 16);                                            \
+        else if (ppt == 8) AT_WB(LI, F, 8);                                              \
+        else if (ppt == 4) AT_WB(LI, F, 4);                                              \
         else return hipErrorInvalidValue;                                                \
     } while (0)
     if (linear) { if (fma) AT_WBP(true, true); else AT_WBP(true, false); }

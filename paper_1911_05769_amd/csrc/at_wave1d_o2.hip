@@ -6,7 +6,7 @@ namespace atk {
 hipError_t launch_wave1d_o4(const Step1D &a, bool linear, bool fma, int ppt, int nw, int64_t nblocks,
                             size_t lds, hipStream_t st);
 hipError_t launch_wave1d_batch_o4(const Step1D *descs, const int2 *tbl, int64_t nblocks,
-                                  bool linear, bool fma, int ppt, int nw, int64_t n0, int flip,
+                                  bool linear, bool fma, int ppt, int64_t n0, int flip,
                                   size_t lds, hipStream_t st);
 
 // LDS of one wave: the stage part, the history of D + 1 levels (twice) of the
@@ -26,12 +26,12 @@ hipError_t launch_wave1d(const Step1D &a, int order, bool linear, bool fma, int 
 }
 
 hipError_t launch_wave1d_batch(const Step1D *descs, const int2 *tbl, int64_t nblocks, int order,
-                               bool linear, bool fma, int ppt, int nw, int64_t n0, int flip, size_t lds,
+                               bool linear, bool fma, int ppt, int64_t n0, int flip, size_t lds,
                                hipStream_t st)
 {
     if (order == 4)
-        return launch_wave1d_batch_o4(descs, tbl, nblocks, linear, fma, ppt, nw, n0, flip, lds, st);
-    return launch_wave1d_batch_order<2>(descs, tbl, nblocks, linear, fma, ppt, nw, n0, flip, lds, st);
+        return launch_wave1d_batch_o4(descs, tbl, nblocks, linear, fma, ppt, n0, flip, lds, st);
+    return launch_wave1d_batch_order<2>(descs, tbl, nblocks, linear, fma, ppt, n0, flip, lds, st);
 }
 
 }  // namespace atk

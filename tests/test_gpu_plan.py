@@ -93,3 +93,54 @@ def test_variants_take_the_steps_of_variant_0(gpu):
     st.set_fuse(48)
     st.set_variant(1)
     assert st.query()[1] == 48 and st.launch_shape(48) == (48, 16, 1)
+
+
+def batch(gpu, sizes, tile, order, arith=0, nsteps=140):
+    nu = 2e-3
+    ins, u0 = [], []
+    for j, n in enumerate(sizes):
+        u = I.u0_powerlaw(n, max(2, min(n // 16, 4096)), j)
+        u = u / np.max(np.abs(u))
+        ins.append(dict(n=n, p=n // tile, order=order, L=1 + j % 3, nu=nu,
+                        dt=I.dt_rule(2 * math.pi / n, 1.0, nu), nsteps_max=nsteps, seed=j, dist=1, arith=arith))
+        u0.append(torch.from_numpy(np.ascontiguousarray(u)).cuda())
+    return gpu.Batch(ins), ins, u0
+
+
+@pytest.mark.parametrize("sizes,tile,order", [([4096, 8192, 16384], 128, 2), ([1 << 18] * 36, 256, 4),
+                                              ([1 << 16] * 20, 64, 4), ([1 << 18] * 60 + [4096] * 5, 256, 2)])
+def test_tuned_batch_has_a_name(gpu, sizes, tile, order):
+    print("batch plan", len(sizes), tile, order, flush=True)
+    tuned, _, u0 = batch(gpu, sizes, tile, order)
+    s = tuned.autotune(u0, 64)
+    named, _, _ = batch(gpu, sizes, tile, order)
+    named.set_variant(tuned.variant)
+    named.set_fuse(s)
+    for n in (1, 2, 7, s, s + 1, 2 * s, 100, 140):
+        assert tuned.launch_shape(n) == named.launch_shape(n), n
+    print("  variant %d, %d steps:" % (tuned.variant, s), tuned.launch_shape(140), flush=True)
+
+
+def test_batch_at_32_points(gpu):
+    """Variant 1 on a batch large enough for 32 points per thread at 64 steps, and 16
+    at 8: every instance's standalone bits, also where a run is shorter than a launch."""
+    b, ins, u0 = batch(gpu, [1 << 18] * 36 + [4096, 12288], 256, 4)
+    refs = {}
+    for j in (0, 17, 36, 37):
+        st = gpu.Stepper(**dict(ins[j], fuse_steps=1))
+        u = u0[j].clone()
+        st.run(u, torch.empty_like(u), 135)
+        refs[j] = u
+    for fuse, points in ((64, 32), (8, 16)):
+        b.reset()
+        b.set_fuse(fuse)
+        us = [u.clone() for u in u0]
+        t = [torch.empty_like(u) for u in u0]
+        assert b.launch_shape(128) == (min(64, fuse), points)
+        b.run(us, t, 128, use_graph=True)
+        b.run(us, t, 7)
+        for j, ref in refs.items():
+            assert torch.equal(us[j], ref), (fuse, j)
+    with pytest.raises(gpu.AtError) as e:
+        b.launch_shape(0)
+    assert e.value.status == gpu.AT_ERR_ARG
