@@ -370,8 +370,9 @@ at_status at_set_fuse(at_ctx *ctx, int32_t fuse_steps);
 
 /* Reverse steps per launch of at_adjoint.  0 (default): as many as the grid
  * allows (tiles of a few points: one per launch); 1: one reverse step per
- * launch; 2..64: at most that many per launch, in whole groups of 4 (AT_ERR_ARG
- * beyond this grid's limit, and for tile widths that are no multiple of 4).
+ * launch; 2..64: that many per launch in whole groups of 4, rounded down, but one
+ * group at least: 2 and 3 mean 4 (AT_ERR_ARG beyond this grid's limit, and for
+ * tile widths that are no multiple of 4).
  * Every setting
  * gives the same lambda bits; dJ/dnu is summed in a different grouping. */
 at_status at_set_adjoint_fuse(at_ctx *ctx, int32_t steps);

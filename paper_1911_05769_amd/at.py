@@ -325,7 +325,8 @@ class Stepper:
         _check(lib().at_set_fuse(self._ctx, int(s)), "at_set_fuse")
 
     def set_adjoint_fuse(self, s: int):
-        """Reverse steps per adjoint launch: 0 automatic, 1 one step per launch."""
+        """Reverse steps per adjoint launch: 0 automatic, 1 one step per launch, else
+        in whole groups of 4 (see at_set_adjoint_fuse)."""
         _check(lib().at_set_adjoint_fuse(self._ctx, int(s)), "at_set_adjoint_fuse")
 
     def set_variant(self, v: int):

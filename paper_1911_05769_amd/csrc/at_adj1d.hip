@@ -244,14 +244,6 @@ __global__ __launch_bounds__(kThreads) void k_adj1d(Adj1D a)
     }
 }
 
-
-__device__ __forceinline__ int64_t fdiv(int64_t a, int64_t b)
-{
-    int64_t q = a / b;
-    return (a % b != 0 && ((a < 0) != (b < 0))) ? q - 1 : q;
-}
-
-
 // a + x with the rounding error of the sum collected as in acc_add, by six
 // additions instead of a comparison and selections
 __device__ __forceinline__ void acc_add_nobranch(Acc &a, double x)

@@ -196,7 +196,7 @@ struct at_ctx {
     hipStream_t st;
     int8_t *delays;
     double *ring, *red, *ckpt, *seg, *lam, *mu, *gnu;
-    int32_t *sync;   // level counters (1D [P][2], 3D [blocks]), then the error flag
+    int32_t *sync;   // weakly-synchronous run: level counters (3D: [blocks]), then the error flag
     int64_t n;
     int fuse;
     int variant;     // 3D kernel variant (tile rows, prefetch depth, register budget)
@@ -241,10 +241,10 @@ at_status make_layout(const at_config *c, const Derived &d, Layout &L)
     off = align_up(off + 8ull * (uint64_t)L.R * ring_level_doubles(c, d));
     L.red = off;
     off = align_up(off + 8ull * (kRedBlocks * 6 + 16));
-    // level counters of the weakly-synchronous run (1D: [P][2] tile edges;
-    // 3D: one per block), then its error flag
+    // level counters of the weakly-synchronous run (3D: one per block; in 1D the
+    // edge values tell their arrival themselves), then its error flag
     L.sync = off;
-    off = align_up(off + 4ull * ((d.dim == 1 ? 2 * (uint64_t)d.P : (uint64_t)d.nb) + 64));
+    off = align_up(off + 4ull * ((d.dim == 1 ? 0 : (uint64_t)d.nb) + 64));
     if (c->record) {
         L.nckpt = c->nsteps_max / c->ckpt_every + 1;
         L.ckpt = off;
@@ -1195,7 +1195,7 @@ at_status at_run_ws(at_ctx *c, double *u, double *scratch, int64_t nsteps, int32
         return fail(AT_ERR_SHAPE, "%lld tiles, but at most %lld workgroups can be resident at once",
                     (long long)d.P, (long long)maxt);
     if (nsteps == 0) return AT_OK;
-    int32_t *err = c->sync + 2 * d.P;
+    int32_t *err = c->sync;
     Ws1D a{};
     a.u = u;
     a.ring = c->ring;
@@ -1464,7 +1464,7 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
             // segment's last group may be short): as few as sadj allows, of even length
             for (int64_t nt = a1; sadj > 0 && nt > a0;) {
                 const int64_t groups = (nt - a0 + kAdjGroup - 1) / kAdjGroup;
-                const int64_t most = std::max(1, sadj / kAdjGroup);
+                const int64_t most = std::max(1, sadj / kAdjGroup);     // groups of a launch
                 const int64_t left = (groups + most - 1) / most;            // launches
                 const int64_t take = (groups + left - 1) / left;            // groups of this one
                 const int s = (int)(nt - a0 - (groups - take) * kAdjGroup);
