@@ -31,12 +31,15 @@ FP64_ISSUE_TINSTR = 39.3        # 256 CU x 4 SIMD x 16 lanes x 2.4 GHz: FP64 VAL
 METRIC = "grid-point updates/s & % HBM peak (AT step, adjoint, batched) vs plain form"
 
 # HBM bytes per launch of the headline kernel, from rocprofv3 FETCH_SIZE x 2.0 +
-# WRITE_SIZE x 1.0 (scales from a plain 1 GiB copy); reported only while the
-# kernel source hashes to the value the counters were taken on, and null
+# WRITE_SIZE x 1.0 (scales from a plain 1 GiB copy); reported only for launches
+# of the measured shape (steps, points per thread, waves of a workgroup) and while
+# the kernel source hashes to the value the counters were taken on, and null
 # (bytes_per_launch None) until they have been taken on the current source.
 TRAFFIC = {"sources": ["paper_1911_05769_amd/csrc/at_wave1d.h",
+                       "paper_1911_05769_amd/csrc/at_wave.h",
                        "paper_1911_05769_amd/csrc/at_stencil1d.h"],
-           "md5": None, "fuse": 48, "bytes_per_launch": None}
+           "md5": "91698db56b8f1e06e3b32a1de61a0189", "fuse": 48, "ppt": 16, "waves": 4,
+           "bytes_per_launch": 73246.5 * 1024 * 2.0 + 132608 * 1024}
 
 
 def eprint(*a):
@@ -119,6 +122,7 @@ def bench_c2(args, torch, at, I, fuse=None, label="main", arith=0):
     if fuse is None:
         s = st.autotune(u0, 100)
     else:
+        st.set_variant(1)
         st.set_fuse(fuse)
         s = fuse
     snap = st.snapshot(u0)
@@ -140,6 +144,8 @@ def bench_c2(args, torch, at, I, fuse=None, label="main", arith=0):
     kern_ms = tm.total_ms()
     run_ms = tm.each_ms()
     launches = math.ceil(wl.nsteps / s)
+    if s > 1 and N >= 1 << 21:      # an even number, so that the run ends in the field it began in
+        launches += launches % 2
     ms_launch = kern_ms / (args.steps * launches)
     # the last launch of a run may carry fewer steps; use the mean steps per launch
     s_mean = wl.nsteps / launches
@@ -151,9 +157,8 @@ def bench_c2(args, torch, at, I, fuse=None, label="main", arith=0):
     # issue-rate ceiling for this instruction mix: 39.3 T FP64 instructions/s
     # (a diagnostic; the roofline's peak is the published 78.6 TFLOP/s)
     issue_ceiling = FP64_ISSUE_TINSTR * fl / ins
-    # one step per launch runs the plain kernel (8 points per thread)
-    ppt = 8 if s == 1 else {1: 16, 2: 8, 3: 4}.get(st.variant, 16)
-    res = dict(wl=wl, s=s, ppt=ppt, wall=wall, ms_per_step=wall * 1e3 / args.steps, run_ms=run_ms,
+    _, ppt, waves = st.launch_shape(wl.nsteps)
+    res = dict(wl=wl, s=s, ppt=ppt, waves=waves, wall=wall, ms_per_step=wall * 1e3 / args.steps, run_ms=run_ms,
                value=N * wl.nsteps * args.steps / wall, ms_launch=ms_launch, gbps=gbps,
                tflops=tflops, issue_ceiling=issue_ceiling, arith=arith, launches=launches,
                bytes_launch=bytes_launch, u0=wl.u0,
@@ -176,15 +181,17 @@ def sources_md5(paths):
 
 def measured_traffic(r):
     """Counter-measured HBM bytes per launch, or None when they do not apply
-    (no counters taken on the current source, another steps-per-launch, or
-    the contracted arithmetic)."""
+    (no counters taken on the current source, another launch shape, or the
+    contracted arithmetic)."""
     if TRAFFIC["md5"] is None or TRAFFIC["bytes_per_launch"] is None:
         return None
     try:
         md5 = sources_md5(TRAFFIC["sources"])
     except OSError:
         return None
-    if md5 != TRAFFIC["md5"] or r["s"] != TRAFFIC["fuse"] or r.get("arith", 0) != 0:
+    shape = [r.get(k, TRAFFIC[k]) for k in ("ppt", "waves")]
+    if md5 != TRAFFIC["md5"] or r["s"] != TRAFFIC["fuse"] or r.get("arith", 0) != 0 or \
+            shape != [TRAFFIC["ppt"], TRAFFIC["waves"]]:
         return None
     return round(TRAFFIC["bytes_per_launch"])
 
@@ -312,9 +319,9 @@ def main():
                     help="comma-separated sub-measurements run with --only all")
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--fuse", type=int, default=None,
-                    help="steps per launch of the headline run (default: autotuned)")
+                    help="steps per launch of the headline run, in variant 1 (default: autotuned)")
     ap.add_argument("--batch-fuse", type=int, default=None,
-                    help="batched leg: steps per launch at 16 points per thread (default: autotuned)")
+                    help="batched leg: steps per launch of variant 1 (default: autotuned)")
     ap.add_argument("--variant3d", type=int, default=None,
                     help="3D legs: run this kernel variant instead of the autotuned one")
     ap.add_argument("--calibrate", action="store_true",
@@ -357,8 +364,9 @@ def main():
                    "p": main_res["wl"].p[0], "order": 4, "L": 4, "nsteps": 2000,
                    "fuse_steps": main_res["s"], "points_per_thread": main_res["ppt"],
                    "arith": "exact order, no contraction",
-                   "kernel": ("k_step1d_plain<4,false,false>" if main_res["s"] == 1
-                              else "k_wave1d<4,false,false,%d,...>" % main_res["ppt"])},
+                   "kernel": ("k_step1d_plain<4,false,false,8>" if main_res["s"] == 1
+                              else "k_wave1d<4,false,false,%d,...,%d>" %
+                              (main_res["ppt"], main_res["waves"]))},
         "roofline": rl,
         "roofline_other": rl_other,
         "timing": dict(spread(main_res["run_ms"]), clock="HIP events around each 2000-step run"),
@@ -488,7 +496,7 @@ def bench_batched(args, torch, at, I):
     algo = sum(algo_bytes_1d(w.n[0], w.p[0], w.order, w.L, w.dist, 1) for w in wls) * nst
     res.update({
         "value": upd / k3, "unit": "grid-point updates/s", "fuse_steps": s,
-        "points_per_thread": {0: 16, 1: 16, 2: 8, 3: 4}[b.variant],
+        "points_per_thread": b.launch_shape(nst)[1],
         "ms_graph_run": round(k3 * 1e3, 3),
         "ms_per_instance_plain": round(k1 * 1e3, 3),
         "ms_one_launch_per_step": round(k2 * 1e3, 3),
