@@ -1608,7 +1608,7 @@ void drop_graph(at_batch *b)
 // where the batch fills the SIMDs many times over.  By the waves of the busiest SIMD
 // and their time per step (fused_cost), and for 32 points what a wave whose lanes
 // are tile faces takes longer.  Measured (us per step, 16 and 32 points): tiles of
-// 256, order 4, 2^24 points: 16 steps 11.3 and 11.3, 32: 11.2 and 10.2, 48: 11.5 and
+// 256, order 4, 2^24 points: 16 steps 11.3 and 11.6, 32: 11.2 and 10.2, 48: 11.5 and
 // 9.9; 2^22 points, 48: 3.07 and 3.41; tiles of 64, 2^24 points, 16: 14.7 and 17.5.
 bool batch_takes_32(const at_batch *b, int s)
 {
