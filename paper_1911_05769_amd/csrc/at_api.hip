@@ -1547,6 +1547,12 @@ at_status at_adjoint(at_ctx *c, const double *lambda_T, double *grad_u0, double 
 // Batched form: independent 1D instances advanced by shared launches
 // ---------------------------------------------------------------------------
 
+// Region kind (points per thread) and steps per launch of a batch's runs of up to
+// `want` steps at a time (batch_plan); want 0: none yet
+struct BatchPlan {
+    int want = 0, kind = 16, steps = 1;
+};
+
 struct at_batch {
     int count = 0, order = 2;
     bool linear = false, fma = false;
@@ -1561,7 +1567,7 @@ struct at_batch {
     int64_t nsteps_max = 0;   // smallest over the instances
     int max_fuse = 1, fuse = 1;
     int variant = 0;          // 0 and 1: 16 points per thread or 32 (batch_plan), 2: 8, 3: 4
-    int plan_for = 0, kind = 16, steps = 1;   // batch_plan's answer for runs of plan_for steps and more
+    BatchPlan plan;           // of the last run's steps
     int mf_ppt[3] = {1, 1, 1};   // steps-per-launch limit for 16, 8, 4 points per thread
     int64_t n = 0;
     // device tables (two slots: the run's s and its tail)
@@ -1628,28 +1634,29 @@ bool batch_takes_32(const at_batch *b, int s)
 // thread, or fewer where an instance's tiles do not take them (4 always fits: the
 // tile widths are multiples of 16), and the number of steps set, as far as every
 // instance's regions allow
-void batch_plan(at_batch *b, int64_t nsteps)
+BatchPlan batch_plan(const at_batch *b, int64_t nsteps)
 {
-    const int s = (int)std::min<int64_t>(b->fuse, nsteps);
-    if (b->plan_for == s) return;
-    b->plan_for = s;
-    b->kind = 4;
+    BatchPlan r;
+    r.want = (int)std::min<int64_t>(b->fuse, nsteps);
+    if (b->plan.want == r.want) return b->plan;
+    r.kind = 4;
     for (int p = b->variant <= 1 ? 16 : variant_points(b->variant); p > 4; p /= 2) {
         bool ok = true;
         for (const Derived &d : b->d) ok = ok && d.W % p == 0 && fused_shape(d, 1, p).ok;
-        if (ok) { b->kind = p; break; }
+        if (ok) { r.kind = p; break; }
     }
-    if (b->kind == 16 && batch_takes_32(b, s)) b->kind = 32;
-    b->steps = s;
+    if (r.kind == 16 && batch_takes_32(b, r.want)) r.kind = 32;
+    r.steps = r.want;
     for (const Derived &d : b->d)
-        while (b->steps > 1 && !fused_shape(d, b->steps, b->kind).ok) --b->steps;
+        while (r.steps > 1 && !fused_shape(d, r.steps, r.kind).ok) --r.steps;
+    return r;
 }
 
 at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *const *scr,
                        uint64_t key)
 {
     const uint64_t k2 = key ^ ((uint64_t)s * 0x9E3779B97F4A7C15ULL) ^
-                        ((uint64_t)b->kind * 0xD1B54A32D192ED03ULL);
+                        ((uint64_t)b->plan.kind * 0xD1B54A32D192ED03ULL);
     if (b->slot_s[slot] == s && b->slot_key[slot] == k2) return AT_OK;
     drop_graph(b);    // a cached graph reads these tables
     std::vector<Step1D> &D = b->hdesc[slot];
@@ -1659,7 +1666,7 @@ at_status batch_tables(at_batch *b, int slot, int s, double *const *u, double *c
     size_t lds = 0;
     for (int j = 0; j < b->count; ++j) {
         const Derived &d = b->d[j];
-        const FusedShape ws = fused_shape(d, s, b->kind);
+        const FusedShape ws = fused_shape(d, s, b->plan.kind);
         if (!ws.ok) return fail(AT_ERR_STATE, "batch: no region for %d steps per launch", s);
         Step1D &a = D[j];
         a.uin = u[j];
@@ -1717,11 +1724,11 @@ at_status batch_launches(at_batch *b, int64_t n0, int64_t nsteps, double *const 
     // launches of even length (two lengths at most), an even number of them: a copy
     // back of every instance's field costs more than one (256 of them: 0.6 ms)
     while (done < nsteps) {
-        const int64_t left = nsteps - done, n = launch_count(left, b->steps, flip);
+        const int64_t left = nsteps - done, n = launch_count(left, b->plan.steps, flip);
         const int s = (int)((left + n - 1) / n);
         const int slot = s == b->slot_s[0] ? 0 : 1;
         AT_HIP(launch_wave1d_batch(b->desc_dev[slot], b->tbl_dev[slot], b->slot_blocks[slot],
-                                   b->order, b->linear, b->fma, b->kind, n0 + done, flip,
+                                   b->order, b->linear, b->fma, b->plan.kind, n0 + done, flip,
                                    b->slot_lds[slot], stream));
         flip ^= 1;
         done += s;
@@ -1903,7 +1910,7 @@ at_status at_batch_set_fuse(at_batch *b, int32_t s)
     if (s < 1 || s > b->max_fuse)
         return fail(AT_ERR_ARG, "fuse_steps must be in 1..%d for this batch", b->max_fuse);
     b->fuse = s;
-    b->plan_for = 0;
+    b->plan = BatchPlan();
     return AT_OK;
 }
 
@@ -1913,7 +1920,7 @@ at_status at_batch_set_variant(at_batch *b, int32_t v)
     if (v < 0 || v > 3) return fail(AT_ERR_ARG, "batch variant must be in 0..3");
     const int idx = v <= 1 ? 0 : v - 1;               // 16, 8, 4 points per thread
     b->variant = v;
-    b->plan_for = 0;
+    b->plan = BatchPlan();
     b->max_fuse = b->mf_ppt[idx];
     b->fuse = std::min(b->fuse, b->max_fuse);
     b->slot_s[0] = b->slot_s[1] = 0;                  // tables are rebuilt for the new layout
@@ -1948,8 +1955,8 @@ at_status at_batch_run(at_batch *b, double *const *u, double *const *scr, int64_
         return AT_OK;
     }
     // the run's launches are s or s - 1 steps long (batch_launches)
-    batch_plan(b, nsteps);
-    const int64_t nl = launch_count(nsteps, b->steps, 0);
+    b->plan = batch_plan(b, nsteps);
+    const int64_t nl = launch_count(nsteps, b->plan.steps, 0);
     const int s_long = (int)((nsteps + nl - 1) / nl);
     at_status st = batch_tables(b, 0, s_long, u, scr, key);
     if (st) return st;
@@ -2012,9 +2019,8 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
         for (int ci = (int)(sizeof(cands) / sizeof(cands[0])) - 1; ci >= 0; --ci) {
             if (cands[ci] > b->max_fuse) continue;
             b->fuse = cands[ci];
-            b->plan_for = 0;
-            batch_plan(b, b->fuse);
-            if (b->steps == b->fuse) tr.push_back({v, b->fuse, 1e30f});
+            b->plan = BatchPlan();
+            if (batch_plan(b, b->fuse).steps == b->fuse) tr.push_back({v, b->fuse, 1e30f});
         }
     }
     // every candidate twice in turn (the first run builds its tables), then those
@@ -2034,7 +2040,7 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
                 for (int j = 0; j < b->count && st == AT_OK && e == hipSuccess; ++j)
                     e = launch_copy(t1[j], u0[j], b->d[j].N, b->st);
                 b->fuse = t.s;
-                b->plan_for = 0;
+                b->plan = BatchPlan();
                 if (st == AT_OK && e == hipSuccess) e = hipEventRecord(e0, b->st);
                 if (st == AT_OK && e == hipSuccess) st = at_batch_run(b, t1, t2, steps, 0);
                 if (st == AT_OK && e == hipSuccess) e = hipEventRecord(e1, b->st);
@@ -2062,7 +2068,7 @@ at_status at_batch_autotune(at_batch *b, double *const *u0, double *const *t1,
     if (st) return st;
     AT_HIP(hipStreamSynchronize(b->st));
     b->fuse = best_s;
-    b->plan_for = 0;
+    b->plan = BatchPlan();
     if (chosen) *chosen = best_s;
     return AT_OK;
 }
@@ -2071,10 +2077,10 @@ at_status at_batch_launch_shape(const at_batch *b, int64_t nsteps, int32_t *step
 {
     if (!b) return fail(AT_ERR_ARG, "null batch");
     if (nsteps < 1) return fail(AT_ERR_ARG, "nsteps < 1");
-    batch_plan(const_cast<at_batch *>(b), nsteps);    // (what the next run computes anyway)
-    const int64_t nl = launch_count(nsteps, b->steps, 0);
+    const BatchPlan plan = batch_plan(b, nsteps);
+    const int64_t nl = launch_count(nsteps, plan.steps, 0);
     if (steps) *steps = (int32_t)((nsteps + nl - 1) / nl);
-    if (points) *points = b->kind;
+    if (points) *points = plan.kind;
     return AT_OK;
 }
 
